@@ -48,6 +48,7 @@ constexpr int kWavesPerSimd = 3;
 template <int UCAP>
 struct QuantileLdsT {
   static constexpr int kCap = UCAP;
+  static constexpr bool kKeepIds = false;  // the walk keeps a staged batch's Gaussian ids (in gid)
   float2 mean[kTilePix];
   float4 co[kTilePix];
   float thr[QR_MAX_K + 1];
@@ -117,6 +118,7 @@ struct PixelSel {
   float T;   // Algorithm 1: full transmittance when the walk ends (the stop
              // test breaks before T takes the stopping entry's T_test)
   int last;  // Algorithm 1: list position + 1 of the last on-ray entry examined
+  int staged;  // list position where the last staged batch of 256 records starts (uniform)
 };
 
 // The walk for one tile (all 256 threads of the workgroup). Selections go to
@@ -209,7 +211,7 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
   };
 
   float T = 1.f, TQ = 1.f;
-  int k = 0, ns = 0, last = 0;
+  int k = 0, ns = 0, last = 0, staged = lo;
   bool done = !inside;
   // t_{k+1}: changes only at a crossing
   float thr_k;
@@ -222,9 +224,13 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
 
   for (int batch = lo; batch < hi; batch += kTilePix) {
     if (__syncthreads_count(!done) == 0) break;
+    staged = batch;
     const int idx = batch + tid;
-    if (idx < hi) {
+    if (tid >= kTilePix) {
+      // a workgroup wider than the tile: only its first 256 threads walk
+    } else if (idx < hi) {
       const int g = static_cast<int>(v.sorted_gid[idx]);
+      if constexpr (WalkLds::kKeepIds) L.gid[tid] = g;
       const f32x2 m = v.means2d[g];
       const f32x4 c = v.conic_opacity[g];
       L.mean[tid] = make_float2(m.x, m.y);
@@ -327,13 +333,15 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
     L.ns[tid] = inside ? ns : -1;
     L.inv[tid] = ns > 0 ? 1.f / sum : 0.f;
     wave_lds_sync();
-    return PixelSel{ns, TQ, T, last};
+    return PixelSel{ns, TQ, T, last, staged};
   }
-  L.ns[tid] = inside ? ns : -1;
-  L.inv[tid] = ns > 0 ? 1.f / (1.f - TQ) : 0.f;
+  if (tid < kTilePix) {
+    L.ns[tid] = inside ? ns : -1;
+    L.inv[tid] = ns > 0 ? 1.f / (1.f - TQ) : 0.f;
+  }
   wave_lds_sync();
 
-  return PixelSel{ns, TQ, T, last};
+  return PixelSel{ns, TQ, T, last, staged};
 }
 
 // The merge for one tile (all 256 threads; wave-local), after the walk.

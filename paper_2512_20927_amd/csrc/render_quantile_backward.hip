@@ -17,27 +17,34 @@
 //  1. the selection walk (quantile_select.h, the very code of the forward,
 //     so the same Gaussians are selected; nothing per pixel is stored by the
 //     forward): each pixel's selected list positions and weights w^Q in LDS.
-//     A tile selects a few dozen distinct Gaussians (about 20 on the room
-//     scenes, against about 1,200 pixel selections): they get slots 0 .. 31
-//     in list order, and each pixel a 32-bit mask of the slots it selected;
-//  2. feature gradients dF = W^T G: [slots x 256 px] . [256 px x dim] on
-//     v_mfma_f32_16x16x32_bf16 (each wave a quarter of the columns),
-//     W[p][s] = w_ps / Z_p, one atomic per (slot, column);
-//  3. dots D = G F^T: [256 px x dim] . [dim x slots] on the same MFMA (each
-//     wave its 64 pixels), with d_pj read out at the selected (pixel, slot)
-//     pairs and written over the weights, which step 2 no longer needs (so
-//     a selection costs 8 bytes of LDS and K up to 64 fits);
-//  4. a sweep over each pixel's selections (thread per pixel) recomputes
+//     A tile selects a few dozen distinct Gaussians (about 20 at K = 8, 50 at
+//     K = 40 on the room scenes, against 1,200 to 2,900 pixel selections):
+//     they get slots in list order, and each pixel a mask of the slots that it
+//     selected, 32 at a time;
+//  2. one pass over dL/d(out) per 32 slots (stream_slots) for both products on
+//     v_mfma_f32_16x16x32_bf16: feature gradients dF = W^T G, W[p][s] =
+//     w_ps / Z_p, one atomic per (slot, column), and dots D = G F^T, which are
+//     written over the weights (so a selection costs 8 bytes of LDS and K up
+//     to 64 fits);
+//  3. a sweep over each pixel's selections (thread per pixel) recomputes
 //     alpha'_j, w_j and T^Q_j from the records with the walk's own float
-//     operations and turns the dots into dL/dalpha' and the chain rule
-//     above, summed per slot in LDS and added to global memory once per
-//     (slot, value). The tail sums S_j are the total minus the running
-//     prefix, both kept in double.
-// Both products take float32 operands split into bfloat16 pairs
+//     operations and turns the dots into dL/dpower; their moments over the
+//     tile's pixels give the geometric gradients of a slot. The tail sums S_j
+//     are the total minus the running prefix, both kept in double.
+// Both products of step 2 take float32 operands split into bfloat16 pairs
 // x = x_hi + x_lo and form hi.hi + hi.lo + lo.hi with float32 accumulation
-// (relative error below 2^-16 per product). Selections without a slot (a
-// tile with more than 32 distinct selections, or a position past kPosCap)
-// are handled by a plain wave-wide path.
+// (relative error below 2^-16 per product). Selections without a slot (more
+// than 256 distinct selections in a tile, or a position past kPosCap) are
+// handled by a plain wave-wide path.
+//
+// Bound: reading dL/d(out) once (629 MB of a 640x480 frame of 512 features:
+// 134 us at the 4.7 TB/s of a large copy) and, beside it, the walk and the
+// sweep (90 us on their own) and the feature atomics (30 us of the kernel).
+// Measured against two passes over dL/d(out) with 4-byte loads for the
+// feature gradients, a slot limit of 32 past which every selection was taken
+// on its own, and LDS float atomics for the geometric sums: 500k Gaussians,
+// 640x480x512, bf16, K = 8: 640 -> 280 us; 200k, float32, K = 40: 2,400 -> 505
+// us; 8 views 1280x720, e4m3, K = 8: 7.01 -> 4.1 ms (3.7 TB/s of dL/d(out)).
 #include "quantile_select.h"
 #include "wave_ops.h"
 
@@ -67,40 +74,87 @@ __device__ __forceinline__ void atomic_add(QR_GLOBAL float* p, float v) {
   __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Eight consecutive decoded features (columns c .. c+7) of Gaussian g.
+// Eight consecutive features (columns c .. c+7) of Gaussian g. e4m3 codes are
+// decoded without their row's scale: they are then exact as bfloat16, and the
+// scale multiplies the finished dots.
 template <int DT>
 __device__ __forceinline__ void load_feat8(const GView& v, int64_t g, int dim, int c, float (&f)[8]) {
-  const float4 a = load_feat4_global<DT>(v.feats, v.scale, g, dim, c);
-  const float4 b = load_feat4_global<DT>(v.feats, v.scale, g, dim, c + 4);
+  float4 a, b;
+  if constexpr (DT == QR_FP8_E4M3) {
+    const u32x2 r = *reinterpret_cast<const QR_GLOBAL u32x2*>(
+        static_cast<const QR_GLOBAL uint8_t*>(v.feats) + g * dim + c);
+    a = e4m3x4_to_f32(r.x, 1.f);
+    b = e4m3x4_to_f32(r.y, 1.f);
+  } else {
+    a = load_feat4_global<DT>(v.feats, v.scale, g, dim, c);
+    b = load_feat4_global<DT>(v.feats, v.scale, g, dim, c + 4);
+  }
   f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w;
   f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
 }
 
-constexpr int kSlots = 32;      // distinct selections of a tile given slots
-constexpr int kPosCap = 2048;   // list positions covered by the slot bitmap
-constexpr int kGeo = 6;         // d/d(a, b, c, o, u, v)
-constexpr int kNB = 4;          // 16-column MFMA blocks per wave and round
+constexpr int kSlots = 32;       // distinct selections of one pass over dL/d(out)
+constexpr int kMaxSlots = 256;   // distinct selections of a tile given slots
+constexpr int kPosCap = 8192;    // list positions covered by the slot bitmap
+constexpr int kPosWords = kPosCap / 32;
+constexpr int kSub = 32;         // columns of a block (MFMA k of the dots)
+constexpr int kPB = 32;          // pixels of a block, two tile rows (MFMA k of the feature gradients)
+constexpr int kTS = kSub + 8;    // LDS stride (bf16) of a pixel in the transposing tile
+constexpr int kDotStride = kPB + 4;  // LDS stride (float) of a slot's partial dots
+static_assert(kPosWords == kTilePix && kMaxSlots == kTilePix, "one bitmap word and one slot per walk thread");
 
-// LDS of the backward (the walk's staging and per-pixel scalars, then the
-// slot map and the geometric sums).
+// LDS of the backward for NW waves: the walk's staging, which the waves'
+// transposing tiles take over once the walk is done and which holds the
+// slots' records in the sweep, per-pixel scalars and the slot map. Dynamic
+// LDS behind it: selections and weights.
+template <int NW>
 struct BwdLds {
-  float2 mean[kTilePix];
-  float4 co[kTilePix];
+  struct Stage {
+    float2 mean[kTilePix];
+    float4 co[kTilePix];
+    int gid[kTilePix];
+  };
+  static constexpr size_t kTileBytes = 2 * kPB * kTS * sizeof(__bf16);  // hi and lo of one wave's block
+  static constexpr size_t kStage = NW * kTileBytes > sizeof(Stage) ? NW * kTileBytes : sizeof(Stage);
+  static_assert(kSlots * kDotStride * sizeof(float) <= kTileBytes, "a block's partial dots fit in its tile");
+  __attribute__((aligned(16))) unsigned char stage[kStage];
   float thr[QR_MAX_K + 1];
-  float inv[kTilePix];
+  __attribute__((aligned(16))) float inv[kTilePix];
   int ns[kTilePix];
-  uint32_t smask[kTilePix];         // per pixel: slots it selected
-  uint32_t bm[kPosCap / 32];        // selected positions, relative to the list start
-  int bpre[kPosCap / 32];           // slots before each bitmap word
-  int sgid[kSlots];                 // Gaussian id of each slot
-  float geo[4][kSlots * kGeo];      // geometric gradient sums, per wave
-  int nslot;
+  __attribute__((aligned(16))) uint32_t smask[kTilePix];  // per pixel: slots of the pass it selected
+  __attribute__((aligned(16))) int sj[kTilePix];          // place of the first of them in the lists
+  uint32_t bm[kPosWords];   // selected positions, relative to the list start
+  int bpre[kPosWords];      // slots before each bitmap word
+  int sgid[kMaxSlots];      // Gaussian id of each slot
+  float sscale[kMaxSlots];  // e4m3: its row's scale
+  int wtot[4];
 };
 
-__device__ __forceinline__ int slot_of(const BwdLds& B, int r) {
-  if (r >= kPosCap) return -1;
-  const int s = B.bpre[r >> 5] + __popc(B.bm[r >> 5] & ((1u << (r & 31)) - 1u));
-  return s < kSlots ? s : -1;
+// The walk's view of the same memory (its template names the arrays).
+template <int NW>
+struct BwdWalkLds {
+  float2* mean;
+  float4* co;
+  float* thr;
+  float* inv;
+  int* ns;
+  int* gid;
+  static constexpr bool kKeepIds = true;
+  __device__ explicit BwdWalkLds(BwdLds<NW>& B)
+      : mean(reinterpret_cast<typename BwdLds<NW>::Stage*>(B.stage)->mean),
+        co(reinterpret_cast<typename BwdLds<NW>::Stage*>(B.stage)->co),
+        thr(B.thr), inv(B.inv), ns(B.ns), gid(reinterpret_cast<typename BwdLds<NW>::Stage*>(B.stage)->gid) {}
+};
+
+// Four bf16 of an LDS tile, transposed over each 16 lanes: with lane 4e + g
+// of the 16 addressing row e, columns 4g .. 4g+3, lane i receives column i
+// of rows 0 .. 3.
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x4 lds_read_tr(const __bf16* p) {
+  return __builtin_bit_cast(
+      bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                  (__attribute__((address_space(3))) s16x4*)(const_cast<__bf16*>(p))));
 }
 
 // Row of dL/d(out) of tile pixel p (clamped into the image: rows of pixels
@@ -112,387 +166,690 @@ __device__ __forceinline__ const QR_GLOBAL float* grad_row(const GView& v, const
   return gg.grad_out + (static_cast<int64_t>(gy) * v.W + gx) * dim;
 }
 
-// Raw operands of one 32-column step of slot_dots.
-struct DotStep {
-  f32x4 a[4][2];  // g_p, columns c .. c+7, of the lane's pixel in each 16-pixel block
-  float f[2][8];  // f_s, columns c .. c+7, of the lane's slot in each 16-slot block
+// How the waves share a tile's blocks, and where a lane reads dL/d(out): the
+// rows of its pixel in tile rows 2 pb and 2 pb + 1 (clamped into the image:
+// rows of pixels outside it are never used), columns in blocks of 32. Waves
+// lie along the columns (a power of two of them), the rest along the pixels;
+// past NW * MS column blocks the caller makes rounds.
+template <int NW>
+struct Shares {
+  static constexpr int MS = 16 / NW;  // column blocks of a wave
+  static constexpr int kBuf = MS > 1 ? 2 : 1;
+  static constexpr int kBlocks = kTilePix / kPB;
+  int n_sc, cgroups, pgroups, pg, sub0, nsub;
+  int y0, ymax, c0, cmax;
+  const QR_GLOBAL float* g0;
+  int64_t gstride;
+
+  __device__ __forceinline__ Shares(const GView& v, const GGrad& gg, int round, int tx, int ty, int wave, int lane, int dim) {
+    n_sc = (dim + kSub - 1) / kSub - round * NW * MS;
+    cgroups = 1;
+    while (cgroups < NW && cgroups * MS < n_sc) cgroups *= 2;
+    const int cg = wave & (cgroups - 1);
+    pg = wave / cgroups;
+    pgroups = NW / cgroups;
+    sub0 = round * NW * MS + cg * MS;
+    nsub = max(0, min(MS, n_sc - cg * MS));
+    y0 = ty * kTile;
+    ymax = v.H - 1;
+    c0 = sub0 * kSub + 8 * (lane >> 4);
+    cmax = dim - 8;
+    g0 = gg.grad_out + static_cast<int64_t>(min(tx * kTile + (lane & 15), v.W - 1)) * dim;
+    gstride = static_cast<int64_t>(v.W) * dim;
+  }
+  __device__ __forceinline__ void load(int pb, int s, f32x4 (&x)[4]) const {
+    const int c = min(c0 + s * kSub, cmax);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+      const QR_GLOBAL float* r = g0 + min(y0 + 2 * pb + rb, ymax) * gstride + c;
+      x[2 * rb] = *reinterpret_cast<const QR_GLOBAL f32x4*>(r);
+      x[2 * rb + 1] = *reinterpret_cast<const QR_GLOBAL f32x4*>(r + 4);
+    }
+  }
+  // the first blocks of a pass
+  __device__ __forceinline__ void prime(f32x4 (&raw)[kBuf][4]) const {
+    if (nsub > 0) {
+#pragma unroll
+      for (int k = 0; k < kBuf; ++k) load(pg, k, raw[k]);
+    }
+  }
 };
 
-// D[p][s] = <g_p, f_s> for the wave's 64 pixels and the tile's slots, stored
-// to s_d at the place of slot s in pixel p's selection list. The operands of
-// step k+1 are requested before step k is multiplied (a fixed number of
-// loads per step, every address clamped into range).
-template <int DT>
-__device__ __forceinline__ void slot_dots(const GView& v, const GGrad& gg, const BwdLds& B,
-                                          int nslot, int tx, int ty, int wave, int lane, int dim,
-                                          float* __restrict__ s_d, int KP) {
-  const int row = lane & 15, kq = (lane >> 4) * 8;
-  const int n_nb = (nslot + 15) >> 4;  // 1 or 2 blocks of 16 slots
-  int gid[2];
-#pragma unroll
-  for (int nb = 0; nb < 2; ++nb) gid[nb] = B.sgid[min(nb * 16 + row, nslot - 1)];
-  const QR_GLOBAL float* arow[4];
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) arow[mb] = grad_row(v, gg, tx, ty, wave * 64 + mb * 16 + row, dim);
-  floatx4 acc[4][2];
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int nk = (dim + 31) >> 5;
-  auto load = [&](int k, DotStep& o) {
-    const int c = min(k * 32 + kq, dim - 8);  // dim is a multiple of 8
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      o.a[mb][0] = *reinterpret_cast<const QR_GLOBAL f32x4*>(arow[mb] + c);
-      o.a[mb][1] = *reinterpret_cast<const QR_GLOBAL f32x4*>(arow[mb] + c + 4);
-    }
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) load_feat8<DT>(v, gid[nb], dim, c, o.f[nb]);
-  };
-  auto multiply = [&](int k, const DotStep& o) {
-    const bool live = k * 32 + kq < dim;  // columns past dim contribute zero
-    bf16x8 ahi[4], alo[4], bhi[2], blo[2];
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      float x[8];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        x[i] = live ? o.a[mb][0][i] : 0.f;
-        x[4 + i] = live ? o.a[mb][1][i] : 0.f;
-      }
-      split8(x, ahi[mb], alo[mb]);
-    }
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) split8(o.f[nb], bhi[nb], blo[nb]);
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      if (nb >= n_nb) continue;
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[mb], bhi[nb], acc[mb][nb], 0, 0, 0);
-        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo[mb], bhi[nb], acc[mb][nb], 0, 0, 0);
-        if (DT != QR_BF16)  // bf16 features are exact in their high part
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[mb], blo[nb], acc[mb][nb], 0, 0, 0);
-      }
-    }
-  };
-  DotStep X, Y;
-  load(0, X);
-  for (int k = 0; k < nk; k += 2) {
-    load(min(k + 1, nk - 1), Y);
-    multiply(k, X);
-    load(min(k + 2, nk - 1), X);
-    if (k + 1 < nk) multiply(k + 1, Y);
-  }
-  // accumulator layout: lane holds D[4 (lane / 16) + i][lane % 16]
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int p = wave * 64 + mb * 16 + 4 * (lane >> 4) + i;
-      const uint32_t m = B.smask[p];
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
-        const int sl = nb * 16 + row;
-        if (sl < nslot && ((m >> sl) & 1u)) s_d[p * KP + __popc(m & ((1u << sl) - 1u))] = acc[mb][nb][i];
-      }
-    }
-  }
-}
+// One pass over dL/d(out) of the tile for slots base .. base + nslot - 1:
+//   DF   feature gradients dF[s][c] = sum_p (w_ps / Z_p) g_p[c], one atomic
+//        per (slot, column) of a wave;
+//   DOT  dots D[p][s] = <g_p, f_s>, which replace the weights of the same
+//        selections (`add`: are added to what an earlier round left there).
+// The waves share out the columns (Shares) and walk the tile's pixels in blocks of 32. A
+// block [32 px x 32 columns] is loaded once, whole 128-byte lines, and serves
+// both products: a lane holds eight consecutive columns of a pixel, which is
+// the A operand of D (k = columns); the B operand of dF (k = pixels) comes
+// from the same bf16 pairs through the wave's own LDS tile and the
+// transposing LDS read. So dL/d(out) is read from memory once per pass and
+// every wave streams its own lines. The dots of a pixel are partial sums over
+// the columns of a wave: after each 32 pixels the waves leave theirs in their
+// tiles and the workgroup adds them up for the selected pairs, one thread per
+// (pixel, selection). (Adding them with LDS float atomics kept the LDS busy
+// for 61% of the kernel.)
+template <int DT, int NW, bool DF, bool DOT>
+__device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, BwdLds<NW>& B,
+                                             float* __restrict__ s_w, int base, int nslot, bool add,
+                                             const Shares<NW>& sh, f32x4 (&raw)[Shares<NW>::kBuf][4],
+                                             int wave, int lane, int dim) {
+  using Sh = Shares<NW>;
+  constexpr int MS = Sh::MS, kBuf = Sh::kBuf, kBlocks = Sh::kBlocks;
+  constexpr int MB = kSlots / 16;
+  const int row = lane & 15, kb = lane >> 4;
+  const int n_mb = (nslot + 15) >> 4;  // blocks of 16 slots (uniform)
+  const int n_sc = sh.n_sc, cgroups = sh.cgroups, pgroups = sh.pgroups, pg = sh.pg, sub0 = sh.sub0, nsub = sh.nsub;
+  const bool partial = (dim & (kSub - 1)) != 0;  // the last block is half a block
 
-// dF[s][c] = sum_p (w_ps / Z_p) g_p[c] for the tile's slots and this wave's
-// column blocks, added to grad_features. A wave takes kNB consecutive
-// 16-column blocks per round (blocks 4 kNB r + kNB wave .. + kNB - 1 in round
-// r), so its loads of one pixel row cover whole 128-byte lines instead of the
-// halves that alternating waves would request at different times. The
-// dL/d(out) operand of step k+1 is requested before step k is multiplied.
-__device__ __forceinline__ void slot_feature_grads(const GView& v, const GGrad& gg, const BwdLds& B,
-                                                   const float* __restrict__ s_sel_w, int nslot,
-                                                   int tx, int ty, int wave, int lane, int dim,
-                                                   int KP) {
-  const int row = lane & 15, kq = (lane >> 4) * 8;
-  const int n_mb = (nslot + 15) >> 4;
-  const int n_blk = dim >> 4;
-  constexpr int kSteps = kTilePix / 32;
-  for (int b0 = wave * kNB; b0 < n_blk; b0 += 4 * kNB) {
-    floatx4 acc[2][kNB];
+  // B operand of D: feature rows of the slots, this wave's columns
+  bf16x8 fhi[MS][MB], flo[MS][MB];
+  if constexpr (DOT) {
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+    for (int s = 0; s < MS; ++s) {
 #pragma unroll
-      for (int nb = 0; nb < kNB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    int col[kNB];
+      for (int nb = 0; nb < MB; ++nb) {
+        if (s < nsub && nb < n_mb) {
+          const int c = (sub0 + s) * kSub + 8 * kb;
+          float x[8];
+          load_feat8<DT>(v, B.sgid[base + min(nb * 16 + row, nslot - 1)], dim, min(c, dim - 8), x);
+          if (c >= dim) {
 #pragma unroll
-    for (int nb = 0; nb < kNB; ++nb) col[nb] = min(b0 + nb, n_blk - 1) * 16 + row;  // clamped
-    // B = G: pixels k*32 + kq .. + 7, column col[nb]. Plain (caching) loads:
-    // the dots pass reads the same rows next and finds them in the caches
-    // (with non-temporal loads the backward took 8% longer).
-    auto load = [&](int k, float (&x)[kNB][8]) {
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const QR_GLOBAL float* r = grad_row(v, gg, tx, ty, k * 32 + kq + t, dim);
-#pragma unroll
-        for (int nb = 0; nb < kNB; ++nb) x[nb][t] = r[col[nb]];
+            for (int i = 0; i < 8; ++i) x[i] = 0.f;
+          }
+          split8(x, fhi[s][nb], flo[s][nb]);
+        }
       }
-    };
-    auto multiply = [&](int k, const float (&x)[kNB][8]) {
-      // A = W^T: slot mb * 16 + row, pixels k*32 + kq .. + 7
-      bf16x8 ahi[2], alo[2];
+    }
+  }
+  floatx4 af[MS][2][MB];
+  if constexpr (DF) {
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb) {
-        const int sl = mb * 16 + row;
-        float w[8];
+    for (int s = 0; s < MS; ++s)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) af[s][cb][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  __bf16* const thi = reinterpret_cast<__bf16*>(B.stage + wave * BwdLds<NW>::kTileBytes);
+  __bf16* const tlo = thi + kPB * kTS;
+  const int t_wr = row * kTS + 8 * kb;                         // + 16 rows for the second pixel row
+  const int t_rd = (8 * kb + (row >> 2)) * kTS + 4 * (row & 3);  // + 4 rows, + 16 columns
+
+#pragma unroll 1
+  for (int pb = 0; pb < kBlocks; ++pb) {
+    if (pb % pgroups == pg && nsub > 0) {
+      const int pb_next = pb + pgroups < kBlocks ? pb + pgroups : pb;
+      // A operand of dF: w / Z of slot mb * 16 + row, pixels 8 kb .. 8 kb + 7
+      // of the block
+      bf16x8 whi[MB], wlo[MB];
+      if constexpr (DF) {
+        const int p0 = pb * kPB + 8 * kb;
+        float w[MB][8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-          const int p = k * 32 + kq + t;
-          const uint32_t m = B.smask[p];
-          w[t] = ((m >> sl) & 1u) ? s_sel_w[p * KP + __popc(m & ((1u << sl) - 1u))] * B.inv[p] : 0.f;
+          const uint32_t m = B.smask[p0 + t];
+          const int j = B.sj[p0 + t];
+          const float inv = B.inv[p0 + t];
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb) {
+            const int sl = mb * 16 + row;
+            // read for every pair (one past a list's end at most), used for the selected
+            const float x = s_w[j + __popc(m & ((1u << sl) - 1u))];
+            w[mb][t] = ((m >> sl) & 1u) ? x * inv : 0.f;
+          }
         }
-        split8(w, ahi[mb], alo[mb]);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) split8(w[mb], whi[mb], wlo[mb]);
+      }
+      floatx4 ad[2][MB];
+      if constexpr (DOT) {
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int nb = 0; nb < MB; ++nb) ad[rb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
       }
 #pragma unroll
-      for (int nb = 0; nb < kNB; ++nb) {
-        bf16x8 bhi, blo;
-        split8(x[nb], bhi, blo);
+      for (int s = 0; s < MS; ++s) {
+        f32x4(&x)[4] = raw[s % kBuf];
+        bf16x8 ahi[2], alo[2];
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-          if (mb >= n_mb) continue;
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[mb], bhi, acc[mb][nb], 0, 0, 0);
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo[mb], bhi, acc[mb][nb], 0, 0, 0);
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[mb], blo, acc[mb][nb], 0, 0, 0);
+        for (int rb = 0; rb < 2; ++rb) {
+          float y[8];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            y[i] = x[2 * rb][i];
+            y[4 + i] = x[2 * rb + 1][i];
+          }
+          split8(y, ahi[rb], alo[rb]);
+        }
+        if (partial && (sub0 + s) * kSub + 8 * kb >= dim) {  // columns past dim
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb) ahi[rb] = alo[rb] = bf16x8{};
+        }
+        // the block two steps on, into the registers just read (always a
+        // load, at the end of one of this pass's blocks again: under a
+        // condition the compiler waits for it on the spot)
+        if (s + kBuf < MS) sh.load(pb, s + kBuf, x);
+        else sh.load(pb_next, s + kBuf - MS, x);
+        if (s >= nsub) continue;  // uniform
+        if constexpr (DF) {
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb) {
+            *reinterpret_cast<bf16x8*>(&thi[t_wr + 16 * rb * kTS]) = ahi[rb];
+            *reinterpret_cast<bf16x8*>(&tlo[t_wr + 16 * rb * kTS]) = alo[rb];
+          }
+          wave_lds_sync();
+        }
+        if constexpr (DOT) {
+#pragma unroll
+          for (int nb = 0; nb < MB; ++nb) {
+            if (nb >= n_mb) continue;
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb) {
+              ad[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[rb], fhi[s][nb], ad[rb][nb], 0, 0, 0);
+              ad[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo[rb], fhi[s][nb], ad[rb][nb], 0, 0, 0);
+              if (DT == QR_F32)  // bf16 features and e4m3 codes are exact in their high part
+                ad[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[rb], flo[s][nb], ad[rb][nb], 0, 0, 0);
+            }
+          }
+        }
+        if constexpr (DF) {
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb) {
+            const bf16x4 h0 = lds_read_tr(&thi[t_rd + 16 * cb]);
+            const bf16x4 h1 = lds_read_tr(&thi[t_rd + 16 * cb + 4 * kTS]);
+            const bf16x4 l0 = lds_read_tr(&tlo[t_rd + 16 * cb]);
+            const bf16x4 l1 = lds_read_tr(&tlo[t_rd + 16 * cb + 4 * kTS]);
+            const bf16x8 bhi = __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7);
+            const bf16x8 blo = __builtin_shufflevector(l0, l1, 0, 1, 2, 3, 4, 5, 6, 7);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+              if (mb >= n_mb) continue;
+              mfma3(af[s][cb][mb], whi[mb], wlo[mb], bhi, blo);
+            }
+          }
+          wave_lds_sync();
         }
       }
-    };
-    float X[kNB][8], Y[kNB][8];
-    load(0, X);
-#pragma unroll 1
-    for (int k = 0; k < kSteps; k += 2) {
-      load(k + 1, Y);
-      multiply(k, X);
-      load(min(k + 2, kSteps - 1), X);
-      multiply(k + 1, Y);
+      if constexpr (DOT) {
+        // lane holds D[4 kb + i][row] of each (pixel row, slot block): four
+        // pixels of a slot
+        float* const d = reinterpret_cast<float*>(thi);
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int nb = 0; nb < MB; ++nb) {
+            if (nb < n_mb)
+              *reinterpret_cast<floatx4*>(&d[(nb * 16 + row) * kDotStride + 16 * rb + 4 * kb]) = ad[rb][nb];
+          }
+      }
     }
-    // lane holds dF[4 (lane / 16) + i][lane % 16] of each block
+    if constexpr (DOT) {
+      __syncthreads();  // every wave has left its sums (and built its weights of these pixels)
+      // the waves whose tiles hold sums of these pixels: column groups of pixel
+      // group pb % pgroups that have columns
+      const int w0 = (pb % pgroups) * cgroups, nw = min(cgroups, (n_sc + MS - 1) / MS);
+      const int q = threadIdx.x & (kPB - 1), p = pb * kPB + q;
+      const float* const d = reinterpret_cast<const float*>(B.stage + w0 * BwdLds<NW>::kTileBytes) + q;
+      uint32_t m = B.smask[p];
+      const int first = threadIdx.x / kPB;
+      for (int k = 0; k < first; ++k) m &= m - 1u;
+      for (int j = B.sj[p] + first; m; j += 2 * NW) {
+        const int sl = __builtin_ctz(m);
+        float x = 0.f;
+        for (int w = 0; w < nw; ++w) x += d[w * (BwdLds<NW>::kTileBytes / sizeof(float)) + sl * kDotStride];
+        if (DT == QR_FP8_E4M3) x *= B.sscale[base + sl];
+        s_w[j] = add ? s_w[j] + x : x;
+        for (int k = 0; k < 2 * NW; ++k) m &= m - 1u;
+      }
+      __syncthreads();  // the tiles are free again
+    }
+  }
+
+  if constexpr (DF) {
+    // lane holds dF[4 kb + i][row] of each (slot block, column block)
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
+    for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int sl = mb * 16 + 4 * (lane >> 4) + i;
+        const int sl = mb * 16 + 4 * kb + i;
         if (sl >= nslot) continue;
-        QR_GLOBAL float* dst = gg.grad_features + static_cast<int64_t>(B.sgid[sl]) * dim + row;
+        QR_GLOBAL float* dst = gg.grad_features + static_cast<int64_t>(B.sgid[base + sl]) * dim + row;
 #pragma unroll
-        for (int nb = 0; nb < kNB; ++nb) {
-          const int blk = b0 + nb;
-          if (blk < n_blk && acc[mb][nb][i] != 0.f) atomic_add(dst + blk * 16, acc[mb][nb][i]);
-        }
+        for (int s = 0; s < MS; ++s)
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb) {
+            const int c = (sub0 + s) * kSub + 16 * cb;
+            if (s < nsub && c < dim && af[s][cb][mb][i] != 0.f) atomic_add(dst + c, af[s][cb][mb][i]);
+          }
       }
     }
   }
 }
 
-// Selections without a slot, for the wave's pixels, one selection at a time
-// over the wave's lanes. DOTS = false: feature gradients w g / Z added to
-// global memory (reads the weights); DOTS = true: the dots <g, f_j>, written
-// over the weight of the same selection (s_d aliases s_sel_w).
-template <int DT, bool DOTS>
-__device__ __forceinline__ void slotless(const GView& v, const GGrad& gg, const BwdLds& B,
-                                         const int* __restrict__ s_sel_pos,
-                                         float* __restrict__ s_sel_w, int tx, int ty, int wave,
-                                         int lane, int dim, int ns, int KP) {
-  const int p_own = wave * 64 + lane;
-  const int nfree = ns - __popc(B.smask[p_own]);  // slotted selections come first
-  uint64_t todo = __ballot(nfree > 0);
+// Selections without a slot (a list position past kPosCap, or more than
+// kMaxSlots distinct selections in the tile: both rare), for the wave's
+// pixels, one selection at a time over the wave's lanes: feature gradients
+// w g / Z added to global memory, then the dot <g, f_j> written over the
+// weight. They are the last of each pixel's list, from entry `jfree` on.
+template <int DT>
+__device__ __forceinline__ void slotless(const GView& v, const GGrad& gg, const float* __restrict__ s_inv,
+                                         const int* __restrict__ s_pos, float* __restrict__ s_w,
+                                         int tx, int ty, int wave, int lane, int dim, int jfree, int ns,
+                                         int KP, bool geo) {
+  uint64_t todo = __ballot(ns > jfree);
   while (todo) {
     const int l = __builtin_ctzll(todo);
     todo &= todo - 1ull;
     const int p = wave * 64 + l;
-    const int n = __builtin_amdgcn_readfirstlane(B.ns[p]);
-    const int j0 = __popc(B.smask[p]);
-    const float inv = B.inv[p];
+    const int n = __builtin_amdgcn_readlane(ns, l);
+    const float inv = s_inv[p];
     const QR_GLOBAL float* grow = grad_row(v, gg, tx, ty, p, dim);
-    for (int j = j0; j < n; ++j) {
-      const int pos = __builtin_amdgcn_readfirstlane(s_sel_pos[p * KP + j]);
+    for (int j = __builtin_amdgcn_readlane(jfree, l); j < n; ++j) {
+      const int pos = ~__builtin_amdgcn_readfirstlane(s_pos[p * KP + j]);
       const int g = static_cast<int>(__builtin_amdgcn_readfirstlane(v.sorted_gid[pos]));
-      if constexpr (DOTS) {
-        float dot = 0.f;
-        for (int c = 4 * lane; c < dim; c += 256) {
-          const f32x4 gx = *reinterpret_cast<const QR_GLOBAL f32x4*>(grow + c);
+      const float w = s_w[p * KP + j] * inv;
+      QR_GLOBAL float* dst = gg.grad_features + static_cast<int64_t>(g) * dim;
+      float dot = 0.f;
+      for (int c = 4 * lane; c < dim; c += 256) {
+        const f32x4 gr = *reinterpret_cast<const QR_GLOBAL f32x4*>(grow + c);
+        if (geo) {
           const float4 f = load_feat4_global<DT>(v.feats, v.scale, g, dim, c);
-          dot += gx.x * f.x + gx.y * f.y + gx.z * f.z + gx.w * f.w;
+          dot += gr.x * f.x + gr.y * f.y + gr.z * f.z + gr.w * f.w;
         }
+        if (gg.grad_features) {
+          atomic_add(dst + c + 0, w * gr.x);
+          atomic_add(dst + c + 1, w * gr.y);
+          atomic_add(dst + c + 2, w * gr.z);
+          atomic_add(dst + c + 3, w * gr.w);
+        }
+      }
+      if (geo) {
         const float t = wave_sum(dot);
-        if (lane == 0) s_sel_w[p * KP + j] = t;
-      } else {
-        const float w = s_sel_w[p * KP + j] * inv;
-        QR_GLOBAL float* dst = gg.grad_features + static_cast<int64_t>(g) * dim;
-        for (int c = 4 * lane; c < dim; c += 256) {
-          const f32x4 gx = *reinterpret_cast<const QR_GLOBAL f32x4*>(grow + c);
-          atomic_add(dst + c + 0, w * gx.x);
-          atomic_add(dst + c + 1, w * gx.y);
-          atomic_add(dst + c + 2, w * gx.z);
-          atomic_add(dst + c + 3, w * gx.w);
-        }
+        wave_lds_sync();  // every lane has read the weight
+        if (lane == 0) s_w[p * KP + j] = t;
       }
     }
   }
 }
 
-// Backward of one tile (all 256 threads of the workgroup). Per-pixel LDS:
-// the walk's selected positions and weights ([256][KP] each); once the
-// feature gradients (which read the weights) are done, the dots d_j are
-// written over the weights, and the sweep recomputes each weight and T^Q_j
-// from the records with the walk's own float operations.
-template <int DT>
+// Bitwise or, and minimum, over the 64 lanes (the exchanges of wave_sum).
+template <class Op>
+__device__ __forceinline__ uint32_t wave_fold(uint32_t x, const Op& op) {
+  const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  x = op(a[0], a[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = op(b[0], b[1]);
+  x = op(x, fbits(dpp<0xB1>(bitsf(x))));
+  x = op(x, fbits(dpp<0x4E>(bitsf(x))));
+  x = op(x, fbits(dpp<0x124>(bitsf(x))));
+  x = op(x, fbits(dpp<0x128>(bitsf(x))));
+  return __builtin_amdgcn_readfirstlane(x);
+}
+__device__ __forceinline__ uint32_t wave_or(uint32_t x) {
+  return wave_fold(x, [](uint32_t a, uint32_t b) { return a | b; });
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t x) {
+  return wave_fold(x, [](uint32_t a, uint32_t b) { return min(a, b); });
+}
+
+// Dynamic LDS: selections and weights, and up to K = kBwdWideK the slots'
+// records (beyond, they take the tiles' place after the last pass).
+constexpr int kBwdPairK = 20, kBwdWideK = 48;
+__host__ __device__ constexpr size_t bwd_list_floats(int K) { return static_cast<size_t>(kTilePix) * ((K + 3) & ~3); }
+__host__ __device__ constexpr bool bwd_early_records(int K) { return K <= kBwdWideK; }
+constexpr size_t bwd_dynamic_lds(int K) {
+  return 2 * bwd_list_floats(K) * sizeof(float) + (bwd_early_records(K) ? kMaxSlots * 6 * sizeof(float) : 0);
+}
+
+// Backward of one tile (all threads of the workgroup; the walk and the sweep
+// use the first 256, one per pixel). s_pos, s_w: the walk's selected
+// positions and weights ([256][KP] each); positions become slots (or ~position
+// without one), and once the feature gradients that read a weight are
+// formed, the dot d_j takes its place. The sweep recomputes each weight and
+// T^Q_j from the records with the walk's own float operations.
+template <int DT, int NW>
 __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGrad& gg, int tile,
                                                        int K, int dim, const qr_params& prm,
-                                                       BwdLds& B, int* __restrict__ s_sel_pos,
-                                                       float* __restrict__ s_sel_w) {
+                                                       BwdLds<NW>& B, float* __restrict__ dyn) {
   const int tiles_x = (v.W + kTile - 1) / kTile;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: addresses stay scalar
+  const bool walker = NW == 4 || tid < kTilePix;
   const int tx = tile % tiles_x, ty = tile / tiles_x;
   const int px = tx * kTile + (tid % kTile);
   const int py = ty * kTile + (tid / kTile);
-  const bool inside = px < v.W && py < v.H;
+  const bool inside = walker && px < v.W && py < v.H;
   const float pxc = px + 0.5f, pyc = py + 0.5f;
   const int lo = static_cast<int>(v.tile_offsets[tile]);
   const int hi = static_cast<int>(v.tile_offsets[tile + 1]);
+  if (lo == hi) return;  // uniform
   const int KP = (K + 3) & ~3;
-  const PixelSel sel = quantile_walk<QR_SELECT_QUANTILE>(v, lo, hi, K, pxc, pyc, inside, prm, B, s_sel_pos, s_sel_w, KP);
+  float* const s_w = dyn;
+  int* const s_pos = reinterpret_cast<int*>(dyn + bwd_list_floats(K));
+  if (walker) B.bm[tid] = 0u;  // read after the walk's barriers
+  BwdWalkLds<NW> WL(B);
+  // the first blocks of dL/d(out) are requested before the walk
+  const Shares<NW> sh(v, gg, 0, tx, ty, wave, lane, dim);
+  f32x4 raw[Shares<NW>::kBuf][4];
+  sh.prime(raw);
+  const PixelSel sel = quantile_walk<QR_SELECT_QUANTILE>(v, lo, hi, K, pxc, pyc, inside, prm, WL, s_pos, s_w, KP);
   const int ns = sel.ns;
-  const int* my_pos = s_sel_pos + tid * KP;
+  int* const my_pos = s_pos + tid * KP;
   const bool geo = gg.grad_means2d || gg.grad_co;
+  // the slots' records, for the sweep: fetched with the slots where LDS is
+  // left for them (fetched after the last pass they would wait for its
+  // atomics: loads and atomics complete in order)
+  const bool early = geo && bwd_early_records(K);
+  float4* const rec_co = reinterpret_cast<float4*>(early ? dyn + 2 * bwd_list_floats(K) : reinterpret_cast<float*>(B.stage));
+  float2* const rec_mean = reinterpret_cast<float2*>(rec_co + kMaxSlots);
+  const auto load_record = [&](int s, int g) {
+    const f32x2 m = v.means2d[g];
+    const f32x4 c = v.conic_opacity[g];
+    rec_mean[s] = make_float2(m.x, m.y);
+    rec_co[s] = make_float4(c.x, c.y, c.z, c.w);
+  };
 
   // ---- slots: the tile's distinct selected positions, in list order ----
-  if (tid < kPosCap / 32) B.bm[tid] = 0u;
-  __syncthreads();
-  for (int j = 0; j < ns; ++j) {
-    const int r = my_pos[j] - lo;
-    if (r < kPosCap) atomicOr(&B.bm[r >> 5], 1u << (r & 31));
+  // (a word of the bitmap at a time: the bits of a wave's pixels are folded in
+  // registers, one LDS atomic per wave and word)
+  if (walker) {
+    uint32_t r = ns > 0 ? static_cast<uint32_t>(my_pos[0] - lo) : kPosCap;
+    for (int j = 0;;) {
+      const uint32_t w = wave_min(r) >> 5;
+      if (w >= kPosWords) break;
+      uint32_t m = 0u;
+      while ((r >> 5) == w) {
+        m |= 1u << (r & 31);
+        ++j;
+        r = j < ns ? static_cast<uint32_t>(my_pos[j] - lo) : kPosCap;
+      }
+      m = wave_or(m);
+      if (lane == 0) atomicOr(&B.bm[w], m);
+    }
   }
   __syncthreads();
-  if (tid < kPosCap / 32) {  // wave 0: exclusive prefix of the word populations
-    const int c = __popc(B.bm[tid]);
-    int incl = c;
+  uint32_t word = 0u;
+  int before = 0;
+  if (walker) {  // prefix of the word populations
+    word = B.bm[tid];
+    int incl = __popc(word);
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const int u = __shfl_up(incl, off, 64);
       if (lane >= off) incl += u;
     }
-    B.bpre[tid] = incl - c;
-    if (tid == kPosCap / 32 - 1) B.nslot = min(incl, kSlots);
+    before = incl - __popc(word);
+    if (lane == 63) B.wtot[wave] = incl;
   }
-  for (int i = tid; i < 4 * kSlots * kGeo; i += kTilePix) (&B.geo[0][0])[i] = 0.f;
   __syncthreads();
-  {
-    uint32_t m = 0u;
-    for (int j = 0; j < ns; ++j) {
-      const int s = slot_of(B, my_pos[j] - lo);
-      if (s < 0) break;  // slots are ranks in list order: the slotted selections come first
-      m |= 1u << s;
-      B.sgid[s] = static_cast<int>(v.sorted_gid[my_pos[j]]);  // same value from every writer
+  const int total = B.wtot[0] + B.wtot[1] + B.wtot[2] + B.wtot[3];
+  const int nslots = min(total, kMaxSlots);
+  if (walker) {
+    for (int w = 0; w < wave; ++w) before += B.wtot[w];
+    B.bpre[tid] = before;
+    for (int s = before; word && s < kMaxSlots; ++s, word &= word - 1u) {
+      // (a position of the batch that is still staged: from LDS)
+      const int pos = lo + 32 * tid + __builtin_ctz(word), k = pos - sel.staged;
+      const int g = k >= 0 ? WL.gid[k] : static_cast<int>(v.sorted_gid[pos]);
+      B.sgid[s] = g;
+      if (DT == QR_FP8_E4M3) B.sscale[s] = v.scale[g];
+      if (!early) continue;
+      if (k >= 0) {
+        rec_mean[s] = WL.mean[k];
+        rec_co[s] = WL.co[k];
+      } else {
+        load_record(s, g);
+      }
     }
-    B.smask[tid] = m;
   }
   __syncthreads();
-  const int nslot = B.nslot;
-
-  if (gg.grad_features) {
-    // ---- feature gradients (read every pixel's weights) ----
-    if (nslot > 0) slot_feature_grads(v, gg, B, s_sel_w, nslot, tx, ty, wave, lane, dim, KP);
-    slotless<DT, false>(v, gg, B, s_sel_pos, s_sel_w, tx, ty, wave, lane, dim, ns, KP);
+  int nslotted = 0;  // slots are ranks in list order: the slotted selections come first
+  for (int j = 0; j < ns; ++j) {
+    const int pos = my_pos[j], r = pos - lo;
+    int s = kMaxSlots;
+    if (r < kPosCap) s = B.bpre[r >> 5] + __popc(B.bm[r >> 5] & ((1u << (r & 31)) - 1u));
+    my_pos[j] = s < kMaxSlots ? s : ~pos;
+    if (s < kMaxSlots) nslotted = j + 1;
   }
-  if (!geo) return;
-  __syncthreads();  // every wave is done with the weights before they are overwritten
 
-  // ---- dots d_pj, written over the weights (wave-local) ----
-  float* s_d = s_sel_w;
-  if (nslot > 0) slot_dots<DT>(v, gg, B, nslot, tx, ty, wave, lane, dim, s_d, KP);
-  slotless<DT, true>(v, gg, B, s_sel_pos, s_sel_w, tx, ty, wave, lane, dim, ns, KP);
-  wave_lds_sync();
+  // ---- feature gradients and dots, 32 slots at a time ----
+  const bool df = gg.grad_features != nullptr;
+  const int rounds = (dim + 511) / 512;
+  int j_next = 0;
+  for (int base = 0; base < nslots; base += kSlots) {
+    if (walker) {
+      uint32_t m = 0u;
+      B.sj[tid] = tid * KP + j_next;
+      for (; j_next < nslotted; ++j_next) {
+        const int s = my_pos[j_next] - base;
+        if (s >= kSlots) break;
+        m |= 1u << s;
+      }
+      B.smask[tid] = m;
+    }
+    __syncthreads();
+    const int n = min(kSlots, nslots - base);
+    if (df && geo && rounds == 1) {
+      if (base > 0) sh.prime(raw);
+      stream_slots<DT, NW, true, true>(v, gg, B, s_w, base, n, false, sh, raw, wave, lane, dim);
+    } else {
+      if (df) {
+        for (int r = 0; r < rounds; ++r) {
+          const Shares<NW> shr(v, gg, r, tx, ty, wave, lane, dim);
+          shr.prime(raw);
+          stream_slots<DT, NW, true, false>(v, gg, B, s_w, base, n, false, shr, raw, wave, lane, dim);
+        }
+      }
+      if (geo) {
+        __syncthreads();  // every weight has been read
+        for (int r = 0; r < rounds; ++r) {
+          const Shares<NW> shr(v, gg, r, tx, ty, wave, lane, dim);
+          shr.prime(raw);
+          stream_slots<DT, NW, false, true>(v, gg, B, s_w, base, n, r > 0, shr, raw, wave, lane, dim);
+        }
+      }
+    }
+    __syncthreads();  // the masks may be rewritten
+  }
+  if (walker) slotless<DT>(v, gg, B.inv, s_pos, s_w, tx, ty, wave, lane, dim, nslotted, ns, KP, geo);
+  if (!geo) return;
 
   // ---- sweep over this pixel's selections ----
+  if (!early) {
+    __syncthreads();
+    if (walker && tid < nslots) load_record(tid, B.sgid[tid]);
+    __syncthreads();
+  }
+  if (!walker) {  // the walkers' barriers below
+    for (int w = 0; 32 * w < nslots; ++w) {
+      __syncthreads();
+      __syncthreads();
+    }
+    return;
+  }
   // Weights and T^Q_j are recomputed front to back exactly as the walk formed
   // them; the tail sums S_j = sum_{l > j} w_l d_l are taken as the total
   // minus the running prefix, both in double.
-  if (ns > 0) {
-    const float TQ = sel.TQ;
-    const float invZ = 1.f / (1.f - TQ);
-    const float* my_d = s_d + tid * KP;
-    double tot = 0.0;
-    {
-      float tq = 1.f;
-      for (int j = 0; j < ns; ++j) {
-        const int g = static_cast<int>(v.sorted_gid[my_pos[j]]);
-        const f32x2 m = v.means2d[g];
-        const f32x4 c = v.conic_opacity[g];
-        const float a = gauss_alpha(make_float2(m.x, m.y), make_float4(c.x, c.y, c.z, c.w), pxc, pyc,
-                                    prm.alpha_max);
-        tot += static_cast<double>(tq * a) * my_d[j];
-        tq = tq * (1.f - a);
-      }
-    }
-    const float gout = static_cast<float>(tot) * invZ;  // <g, out>
-    float tq = 1.f;
-    double pre = 0.0;
-    for (int j = 0; j < ns; ++j) {
-      const int g = static_cast<int>(v.sorted_gid[my_pos[j]]);
-      const f32x2 m = v.means2d[g];
-      const f32x4 c = v.conic_opacity[g];
-      const AlphaEval e = eval_alpha(make_float2(m.x, m.y), make_float4(c.x, c.y, c.z, c.w), pxc,
-                                     pyc, prm.alpha_max);
-      const float wj = tq * e.alpha, dj = my_d[j];
-      pre += static_cast<double>(wj) * dj;
-      const float S = static_cast<float>(tot - pre);  // sum over the later selections
-      const float dL_da = invZ * (tq * dj - (S + gout * TQ) / (1.f - e.alpha));
-      tq = tq * (1.f - e.alpha);
-      if (e.clamped || dL_da == 0.f) continue;
-      const float dpow = dL_da * e.alpha;
-      const float gv[kGeo] = {dpow * (-0.5f * e.dx * e.dx), dpow * (-e.dx * e.dy),
-                              dpow * (-0.5f * e.dy * e.dy), dL_da * e.G,
-                              dpow * (c.x * e.dx + c.y * e.dy), dpow * (c.y * e.dx + c.z * e.dy)};
-      const int s = slot_of(B, my_pos[j] - lo);
-      if (s >= 0) {
+  float* const my_d = s_w + tid * KP;
+  const auto free_record = [&](int j, float2& mean, float4& co) {  // of a selection without a slot
+    const int g = static_cast<int>(v.sorted_gid[~my_pos[j]]);
+    const f32x2 m = v.means2d[g];
+    const f32x4 c = v.conic_opacity[g];
+    mean = make_float2(m.x, m.y);
+    co = make_float4(c.x, c.y, c.z, c.w);
+    return g;
+  };
+  double tot = 0.0;
+  float tq = 1.f;
+  constexpr int kU = 4;  // selections read from LDS per round trip
+  for (int j0 = 0; j0 < nslotted; j0 += kU) {
+    float a[kU], d[kU];
 #pragma unroll
-        for (int i = 0; i < kGeo; ++i) atomicAdd(&B.geo[wave][s * kGeo + i], gv[i]);
-      } else {
-        if (gg.grad_co)
-          for (int i = 0; i < 4; ++i) atomic_add(gg.grad_co + 4 * g + i, gv[i]);
-        if (gg.grad_means2d)
-          for (int i = 0; i < 2; ++i) atomic_add(gg.grad_means2d + 2 * g + i, gv[4 + i]);
-      }
+    for (int u = 0; u < kU; ++u) {
+      const int j = min(j0 + u, nslotted - 1), sl = my_pos[j];
+      a[u] = gauss_alpha(rec_mean[sl], rec_co[sl], pxc, pyc, prm.alpha_max);
+      d[u] = my_d[j];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      if (j0 + u >= nslotted) continue;
+      tot += static_cast<double>(tq * a[u]) * d[u];
+      tq = tq * (1.f - a[u]);
     }
   }
-  __syncthreads();
-  for (int i = tid; i < nslot * kGeo; i += kTilePix) {
-    const float val = B.geo[0][i] + B.geo[1][i] + B.geo[2][i] + B.geo[3][i];
-    const int s = i / kGeo, k = i - s * kGeo;
-    const int g = B.sgid[s];
-    if (val == 0.f) continue;
-    if (k < 4) {
-      if (gg.grad_co) atomic_add(gg.grad_co + 4 * g + k, val);
-    } else if (gg.grad_means2d) {
-      atomic_add(gg.grad_means2d + 2 * g + (k - 4), val);
+  for (int j = nslotted; j < ns; ++j) {
+    float2 mean;
+    float4 co;
+    free_record(j, mean, co);
+    const float a = gauss_alpha(mean, co, pxc, pyc, prm.alpha_max);
+    tot += static_cast<double>(tq * a) * my_d[j];
+    tq = tq * (1.f - a);
+  }
+  const float TQ = sel.TQ;
+  const float invZ = ns > 0 ? 1.f / (1.f - TQ) : 0.f;
+  const float gout = static_cast<float>(tot) * invZ;  // <g, out>
+  tq = 1.f;
+  double pre = 0.0;
+  // dL/dpower of a selection with dot dj (0 if clamped); alpha' = o G
+  const auto dpower = [&](const AlphaEval& e, float dj) {
+    const float wj = tq * e.alpha;
+    pre += static_cast<double>(wj) * dj;
+    const float S = static_cast<float>(tot - pre);  // sum over the later selections
+    const float dL_da = invZ * (tq * dj - (S + gout * TQ) / (1.f - e.alpha));
+    tq = tq * (1.f - e.alpha);
+    return e.clamped ? 0.f : dL_da * e.alpha;
+  };
+  // dL/dpower takes the place of the dot
+  for (int j = 0; j < nslotted; ++j) {
+    const int sl = my_pos[j];
+    const AlphaEval e = eval_alpha(rec_mean[sl], rec_co[sl], pxc, pyc, prm.alpha_max);
+    my_d[j] = dpower(e, my_d[j]);
+  }
+  for (int j = nslotted; j < ns; ++j) {
+    float2 mean;
+    float4 co;
+    const int g = free_record(j, mean, co);
+    const AlphaEval e = eval_alpha(mean, co, pxc, pyc, prm.alpha_max);
+    const float dpow = dpower(e, my_d[j]);
+    if (dpow == 0.f) continue;
+    if (gg.grad_co) {
+      QR_GLOBAL float* const o = gg.grad_co + 4 * static_cast<int64_t>(g);
+      atomic_add(o + 0, dpow * (-0.5f * e.dx * e.dx));
+      atomic_add(o + 1, dpow * (-e.dx * e.dy));
+      atomic_add(o + 2, dpow * (-0.5f * e.dy * e.dy));
+      atomic_add(o + 3, dpow / co.w);
     }
+    if (gg.grad_means2d) {
+      QR_GLOBAL float* const o = gg.grad_means2d + 2 * static_cast<int64_t>(g);
+      atomic_add(o + 0, dpow * (co.x * e.dx + co.y * e.dy));
+      atomic_add(o + 1, dpow * (co.y * e.dx + co.z * e.dy));
+    }
+  }
+  wave_lds_sync();
+  // Every gradient of a slot follows from the moments of its dL/dpower over
+  // the tile's pixels, sum_p dpow_p {1, dx, dy, dx^2, dx dy, dy^2}. A lane takes
+  // one slot and half a tile row at a time (dy is then one value), so the
+  // sums stay in registers; the lanes of a slot are added up by exchanges and
+  // the four waves in LDS. (Evaluating the values per slot for all 64 pixels
+  // of a wave, a quarter of them selected, and summing those over the wave
+  // took twice as long; moments about the tile's centre, as a product on the
+  // matrix cores, lose the digits that dx and dy have near the mean.)
+  const int row = lane & 15, kb = lane >> 4;
+  // [wave][slot][8], behind the records where those are in the tiles' place
+  float* const mom = reinterpret_cast<float*>(B.stage) + kMaxSlots * 6;
+  static_assert((kMaxSlots * 6 + 4 * kSlots * 8) * sizeof(float) <= BwdLds<NW>::kStage, "records and moments");
+  for (int w = 0, j = 0; 32 * w < nslots; ++w) {
+    uint32_t m = 0u;
+    B.sj[tid] = tid * KP + j;
+    for (; j < nslotted; ++j) {
+      const int sl = my_pos[j] - 32 * w;
+      if (sl >= 32) break;
+      m |= 1u << sl;
+    }
+    B.smask[tid] = m;
+    wave_lds_sync();
+    const int n_mb = nslots - 32 * w > 16 ? 2 : 1;
+#pragma unroll 1
+    for (int mb = 0; mb < n_mb; ++mb) {
+      const int sl = mb * 16 + row;
+      const float2 mean = rec_mean[min(32 * w + sl, nslots - 1)];
+      float q[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {  // 32 pixels: two tile rows
+        const int p0 = wave * 64 + 32 * h + 8 * kb;
+        const float dy = (ty * kTile + p0 / kTile + 0.5f) - mean.y;
+        const float dx0 = (tx * kTile + (p0 & 8) + 0.5f);
+        float s0 = 0.f, sx = 0.f, sxx = 0.f;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const uint32_t mp = B.smask[p0 + t];
+          const float x = s_w[B.sj[p0 + t] + __popc(mp & ((1u << sl) - 1u))];
+          const float d = ((mp >> sl) & 1u) ? x : 0.f;
+          const float dx = (dx0 + t) - mean.x;
+          const float v = d * dx;
+          s0 += d;
+          sx += v;
+          sxx = fmaf(v, dx, sxx);
+        }
+        const float sy = s0 * dy;
+        q[0] += s0;
+        q[1] += sx;
+        q[2] += sy;
+        q[3] += sxx;
+        q[4] = fmaf(sx, dy, q[4]);
+        q[5] = fmaf(sy, dy, q[5]);
+      }
+      // over the slot's four lanes, 16 apart
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        q[i] = tsum_bit5(q[i], q[i]);
+        q[i] = tsum_bit4(q[i], q[i]);
+        if (kb == 0) mom[(wave * kSlots + sl) * 8 + i] = q[i];
+      }
+    }
+    __syncthreads();
+    // neighbouring threads add a slot's neighbouring values: threads 0 .. 127
+    // (a, b, c, o) of slot tid / 4, 128 .. 191 (u, v) of slot (tid - 128) / 2
+    const bool conic = tid < 4 * kSlots;
+    const int ls = conic ? tid >> 2 : (tid - 4 * kSlots) >> 1, k = conic ? tid & 3 : 4 + (tid & 1);
+    const int sl = 32 * w + ls;
+    if (tid < 6 * kSlots && sl < nslots) {
+      float q[6];
+#pragma unroll
+      for (int i = 0; i < 6; ++i)
+        q[i] = mom[ls * 8 + i] + mom[(kSlots + ls) * 8 + i] + mom[(2 * kSlots + ls) * 8 + i] +
+               mom[(3 * kSlots + ls) * 8 + i];
+      const float4 co = rec_co[sl];
+      const int64_t g = B.sgid[sl];
+      const float val = k == 0   ? -0.5f * q[3]
+                        : k == 1 ? -q[4]
+                        : k == 2 ? -0.5f * q[5]
+                        : k == 3 ? q[0] / co.w  // alpha' = o G: dL/do = dL/dpower / o
+                        : k == 4 ? co.x * q[1] + co.y * q[2]
+                                 : co.y * q[1] + co.z * q[2];
+      if (conic && gg.grad_co) atomic_add(gg.grad_co + 4 * g + k, val);
+      if (!conic && gg.grad_means2d) atomic_add(gg.grad_means2d + 2 * g + (k - 4), val);
+    }
+    __syncthreads();  // the moments may be rewritten
   }
 }
 
 // Two waves per SIMD (registers of the MFMA operands and accumulators).
 constexpr int kBwdWavesPerSimd = 2;
 
-__device__ __forceinline__ size_t bwd_sel_floats(int K) { return static_cast<size_t>(kTilePix) * ((K + 3) & ~3); }
-
-template <int DT>
-__global__ void __launch_bounds__(kTilePix, kBwdWavesPerSimd)
+template <int DT, int NW>
+__global__ void __launch_bounds__(64 * NW, kBwdWavesPerSimd)
 quantile_backward_kernel(ViewArgs v, GradPtrs gp, int n_tiles, qr_params prm, int K, int dim) {
-  extern __shared__ unsigned char dyn_lds[];
-  __shared__ BwdLds B;
-  const size_t n = bwd_sel_floats(K);
-  int* s_sel_pos = reinterpret_cast<int*>(dyn_lds);
-  float* s_sel_w = reinterpret_cast<float*>(dyn_lds) + n;
-  quantile_backward_tile<DT>(to_global(v), to_global(gp), xcd_remap(blockIdx.x, n_tiles), K, dim,
-                             prm, B, s_sel_pos, s_sel_w);
+  extern __shared__ __attribute__((aligned(16))) float dyn_lds[];
+  __shared__ BwdLds<NW> B;
+  quantile_backward_tile<DT, NW>(to_global(v), to_global(gp), xcd_remap(blockIdx.x, n_tiles), K, dim,
+                                 prm, B, dyn_lds);
 }
 
 __device__ __forceinline__ GradPtrs grad_ptrs(const qr_view_grad& g) {
@@ -501,22 +858,18 @@ __device__ __forceinline__ GradPtrs grad_ptrs(const qr_view_grad& g) {
 
 // Many views in one launch, one workgroup per (view, tile) item, items dealt
 // to the XCDs in contiguous runs of the schedule.
-template <int DT>
-__global__ void __launch_bounds__(kTilePix, kBwdWavesPerSimd)
+template <int DT, int NW>
+__global__ void __launch_bounds__(64 * NW, kBwdWavesPerSimd)
 quantile_backward_batched_grid_kernel(const qr_view* __restrict__ views,
                                       const qr_view_grad* __restrict__ grads,
                                       const uint32_t* __restrict__ schedule, int n_items,
                                       qr_params prm, int K, int dim) {
-  extern __shared__ unsigned char dyn_lds[];
-  __shared__ BwdLds B;
-  const size_t n = bwd_sel_floats(K);
-  int* s_sel_pos = reinterpret_cast<int*>(dyn_lds);
-  float* s_sel_w = reinterpret_cast<float*>(dyn_lds) + n;
+  extern __shared__ __attribute__((aligned(16))) float dyn_lds[];
+  __shared__ BwdLds<NW> B;
   const uint32_t packed = __builtin_amdgcn_readfirstlane(schedule[xcd_remap(blockIdx.x, n_items)]);
   const uint32_t vi = packed >> kViewShift;
-  quantile_backward_tile<DT>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
-                             static_cast<int>(packed & kTileMask), K, dim, prm, B, s_sel_pos,
-                             s_sel_w);
+  quantile_backward_tile<DT, NW>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
+                                 static_cast<int>(packed & kTileMask), K, dim, prm, B, dyn_lds);
 }
 
 // Many views in one persistent launch: items are taken from per-XCD ranges
@@ -527,18 +880,15 @@ __device__ __forceinline__ uint32_t bwd_queue_begin(int64_t n_items, int q) {
   return static_cast<uint32_t>(n_items * q / kBwdXcdQueues);
 }
 
-template <int DT>
-__global__ void __launch_bounds__(kTilePix, kBwdWavesPerSimd)
+template <int DT, int NW>
+__global__ void __launch_bounds__(64 * NW, kBwdWavesPerSimd)
 quantile_backward_batched_kernel(const qr_view* __restrict__ views,
                                  const qr_view_grad* __restrict__ grads,
                                  const uint32_t* __restrict__ schedule, int64_t n_items,
                                  uint32_t* __restrict__ counter, qr_params prm, int K, int dim) {
-  extern __shared__ unsigned char dyn_lds[];
-  __shared__ BwdLds B;
+  extern __shared__ __attribute__((aligned(16))) float dyn_lds[];
+  __shared__ BwdLds<NW> B;
   __shared__ uint32_t s_item[2];
-  const size_t n = bwd_sel_floats(K);
-  int* s_sel_pos = reinterpret_cast<int*>(dyn_lds);
-  float* s_sel_w = reinterpret_cast<float*>(dyn_lds) + n;
   const int home = static_cast<int>(blockIdx.x % kBwdXcdQueues);
   // the item word alternates as in the forward: a wave running ahead writes
   // the other word
@@ -562,9 +912,8 @@ quantile_backward_batched_kernel(const qr_view* __restrict__ views,
     if (item >= n_items) break;
     const uint32_t packed = __builtin_amdgcn_readfirstlane(schedule[item]);
     const uint32_t vi = packed >> kViewShift;
-    quantile_backward_tile<DT>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
-                               static_cast<int>(packed & kTileMask), K, dim, prm, B, s_sel_pos,
-                               s_sel_w);
+    quantile_backward_tile<DT, NW>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
+                                   static_cast<int>(packed & kTileMask), K, dim, prm, B, dyn_lds);
   }
 }
 
@@ -572,13 +921,30 @@ __global__ void reset_bwd_counter_kernel(uint32_t* __restrict__ c) {
   if (threadIdx.x < kBwdXcdQueues) c[threadIdx.x] = 0u;
 }
 
-inline size_t bwd_dynamic_lds(int K) {
-  return static_cast<size_t>(kTilePix) * ((K + 3) & ~3) * 2 * sizeof(float);
-}
+// Workgroup shape by K, from what the selection lists (8 bytes per pixel and
+// K) leave of a CU's 160 KB of LDS: up to K = 20 two workgroups of four waves
+// fit; up to K = 48 one of eight waves, each with half the columns; beyond,
+// one of four waves.
+constexpr size_t kCuLds = 160 * 1024;
+static_assert(2 * (sizeof(BwdLds<4>) + 64 + bwd_dynamic_lds(kBwdPairK)) <= kCuLds, "two workgroups per CU");
+static_assert(sizeof(BwdLds<8>) + 64 + bwd_dynamic_lds(kBwdWideK) <= kCuLds, "one workgroup of eight waves");
+static_assert(sizeof(BwdLds<4>) + 64 + bwd_dynamic_lds(QR_MAX_K) <= kCuLds, "the largest K fits");
 
 }  // namespace qr
 
 using namespace qr;
+
+#define QR_BWD_DISPATCH_NW(dt, NW)                    \
+  switch (dt) {                                       \
+    case QR_F32: QR_LAUNCH(QR_F32, NW); break;        \
+    case QR_BF16: QR_LAUNCH(QR_BF16, NW); break;      \
+    default: QR_LAUNCH(QR_FP8_E4M3, NW); break;       \
+  }
+#define QR_BWD_DISPATCH(dt, wide)                     \
+  do {                                                \
+    if (wide) { QR_BWD_DISPATCH_NW(dt, 8) }           \
+    else { QR_BWD_DISPATCH_NW(dt, 4) }                \
+  } while (0)
 
 extern "C" int qr_render_quantile_backward(void* stream, int32_t width, int32_t height,
                                            const qr_params* prm, int32_t K,
@@ -604,15 +970,12 @@ extern "C" int qr_render_quantile_backward(void* stream, int32_t width, int32_t 
                    reinterpret_cast<const float4*>(conic_opacity), features, feature_scale,
                    nullptr, nullptr, nullptr};
   const GradPtrs gp{grad_out, grad_features, grad_means2d, grad_conic_opacity};
+  const bool wide = K > kBwdPairK && K <= kBwdWideK;
   const size_t lds = bwd_dynamic_lds(K);
-#define QR_LAUNCH(DT)                                                                             \
-  hipLaunchKernelGGL(quantile_backward_kernel<DT>, dim3(n_tiles), dim3(kTilePix), lds, s, v, gp, \
+#define QR_LAUNCH(DT, NW)                                                                              \
+  hipLaunchKernelGGL((quantile_backward_kernel<DT, NW>), dim3(n_tiles), dim3(64 * NW), lds, s, v, gp, \
                      n_tiles, *prm, K, dim)
-  switch (dtype) {
-    case QR_F32: QR_LAUNCH(QR_F32); break;
-    case QR_BF16: QR_LAUNCH(QR_BF16); break;
-    default: QR_LAUNCH(QR_FP8_E4M3); break;
-  }
+  QR_BWD_DISPATCH(dtype, wide);
 #undef QR_LAUNCH
   return check_launch("qr_render_quantile_backward");
 }
@@ -644,30 +1007,23 @@ extern "C" int qr_render_quantile_batched_backward(void* stream, int32_t n_views
     return fail(QR_ERR_UNSUPPORTED, "%s: the quantile selection only", name);
   if (n_items == 0) return QR_OK;
   hipStream_t s = as_stream(stream);
+  const bool wide = K > kBwdPairK && K <= kBwdWideK;
   const size_t lds = bwd_dynamic_lds(K);
   if (n_workgroups == 0) {
     const int ni = static_cast<int>(n_items);
-#define QR_LAUNCH(DT)                                                                        \
-  hipLaunchKernelGGL(quantile_backward_batched_grid_kernel<DT>, dim3(ni), dim3(kTilePix), lds, \
+#define QR_LAUNCH(DT, NW)                                                                          \
+  hipLaunchKernelGGL((quantile_backward_batched_grid_kernel<DT, NW>), dim3(ni), dim3(64 * NW), lds, \
                      s, views, grads, schedule, ni, *prm, K, dim)
-    switch (dtype) {
-      case QR_F32: QR_LAUNCH(QR_F32); break;
-      case QR_BF16: QR_LAUNCH(QR_BF16); break;
-      default: QR_LAUNCH(QR_FP8_E4M3); break;
-    }
+    QR_BWD_DISPATCH(dtype, wide);
 #undef QR_LAUNCH
     return check_launch(name);
   }
   auto* counter = static_cast<uint32_t*>(workspace);
   hipLaunchKernelGGL(reset_bwd_counter_kernel, dim3(1), dim3(64), 0, s, counter);
-#define QR_LAUNCH(DT)                                                                         \
-  hipLaunchKernelGGL(quantile_backward_batched_kernel<DT>, dim3(n_workgroups), dim3(kTilePix), \
+#define QR_LAUNCH(DT, NW)                                                                           \
+  hipLaunchKernelGGL((quantile_backward_batched_kernel<DT, NW>), dim3(n_workgroups), dim3(64 * NW), \
                      lds, s, views, grads, schedule, n_items, counter, *prm, K, dim)
-  switch (dtype) {
-    case QR_F32: QR_LAUNCH(QR_F32); break;
-    case QR_BF16: QR_LAUNCH(QR_BF16); break;
-    default: QR_LAUNCH(QR_FP8_E4M3); break;
-  }
+  QR_BWD_DISPATCH(dtype, wide);
 #undef QR_LAUNCH
   return check_launch(name);
 }

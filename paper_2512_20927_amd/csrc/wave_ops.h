@@ -73,14 +73,25 @@ __device__ __forceinline__ float tsum_rows(const float (&r4)[16], int lane) {
   return tsum_dpp<0xB1>(r1[0], r1[1], lane & 1);                                    // quad_perm [1,0,3,2]
 }
 
-// x = hi + lo with hi the bf16 rounding of x and lo that of the remainder.
+// x = hi + lo with hi the bf16 rounding of x and lo that of the remainder,
+// two elements per conversion instruction (one at a time, the conversion and
+// the packing of its results took 5 VALU instructions per element instead of
+// 3).
 __device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& lo) {
+  typedef float f32x2_ __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2_ __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x4_ __attribute__((ext_vector_type(4)));
+  u32x4_ h, l;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const __bf16 h = static_cast<__bf16>(x[i]);
-    hi[i] = h;
-    lo[i] = static_cast<__bf16>(x[i] - static_cast<float>(h));
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t p = __builtin_bit_cast(
+        uint32_t, __builtin_convertvector(f32x2_{x[2 * i], x[2 * i + 1]}, bf16x2_));
+    const f32x2_ r = {x[2 * i] - bitsf(p << 16), x[2 * i + 1] - bitsf(p & 0xFFFF0000u)};
+    h[i] = p;
+    l[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2_));
   }
+  hi = __builtin_bit_cast(bf16x8, h);
+  lo = __builtin_bit_cast(bf16x8, l);
 }
 
 // acc += A B for split operands: hi.hi + lo.hi + hi.lo (the lo.lo term is
