@@ -571,7 +571,7 @@ def run_room(args):
     # bracket the batched launch alone (in the overlapped run the front of the
     # next step shares the GPU with it)
     achieved = bytes_batch / (k_seq * 1e-3) / 1e9
-    ucap = 32 if 25 <= K <= 52 else 16  # the kernels' merge capacity for this K
+    ucap = 16  # the merge-capacity argument of the kernels of this rule
     kernel = ("render_quantile_batched_grid_kernel<0, 0, 0, %d>" % ucap if tuned["wg_per_cu"] == 0
               else "render_quantile_batched_kernel<0, 0, 0, %d>" % ucap)
     traffic = measured_traffic(kernel, "room")

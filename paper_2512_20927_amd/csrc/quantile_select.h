@@ -4,17 +4,20 @@
 //  - the walk: the tile's depth-sorted list is staged into LDS in batches of
 //    256 projected records and every pixel (one thread each) runs the
 //    transmittance chain T_test = T (1 - alpha') with the threshold test
-//    T_test < t_{k+1}, recording the <= K selected list positions and their
-//    weights w^Q = T^Q alpha'; a pixel is done once all K thresholds are
-//    consumed (the same event as the stop test T_test < 1/(K+1)) and the
-//    workgroup leaves the list once every pixel is done;
-//  - the merge: each group of four adjacent pixels (a row segment of the
-//    tile) has its four selection lists, ordered by list position, merged
-//    into its distinct selections, each carrying the four pixels' weights
-//    divided by the pixel's 1 - T^Q (0 where a pixel did not select it) and a
-//    mask of the pixels that selected it. The pixels of wave w are tile rows
-//    4w .. 4w+3, exactly the pixels of the groups it merges, so the merge and
-//    everything after it are wave-local.
+//    T_test < t_{k+1}; a pixel is done once all K thresholds are consumed (the
+//    same event as the stop test T_test < 1/(K+1)) and the workgroup leaves
+//    the list once every pixel is done. What becomes of a selection (weight
+//    w^Q = T^Q alpha') is up to a sink:
+//     - ListSink: each pixel's selected list positions and weights (the
+//       backward, and the Top-K sampler, which replaces entries);
+//     - GroupSink: the distinct selections of each group of four adjacent
+//       pixels (a row segment of the tile, four neighbouring lanes), in list
+//       order, each with the four pixels' weights (0 where a pixel did not
+//       select it) and a mask of the pixels that did: what the forward gathers;
+//  - the merge (Top-K): the four pixels' lists of each group are merged into
+//    the same form.
+//    The pixels of wave w are tile rows 4w .. 4w+3, exactly the pixels of the
+//    groups it merges, so everything after the walk is wave-local.
 #pragma once
 
 #include "common.h"
@@ -27,10 +30,9 @@ constexpr uint32_t kTileMask = (1u << QR_BATCH_TILE_BITS) - 1u;
 
 constexpr int kPG = 4;                     // pixels gathered together
 constexpr int kGroups = kTilePix / kPG;    // 64 pixel groups per tile
-// Distinct selections kept per merged group: 16, or 32 for 24 < K <= 52,
-// where the selection lists already hold the kernel to one workgroup per CU
-// (at K = 40 about 44% of the room workload's groups have more than 16
-// distinct selections and 0.1% more than 32).
+// Distinct selections kept per merged Top-K group: 16, or 32 for 24 < K <=
+// 52, where the selection lists already hold the kernel to one workgroup per
+// CU.
 constexpr int kUCap = 16;
 constexpr int kUCapLarge = 32;
 constexpr int kUCapLargeMinK = 25;
@@ -38,21 +40,19 @@ constexpr int kUCapLargeMaxK = 52;
 __host__ __device__ constexpr int ucap_for(int K) {
   return K >= kUCapLargeMinK && K <= kUCapLargeMaxK ? kUCapLarge : kUCap;
 }
-// Three 45 KB workgroups fill a CU's LDS: registers are bounded to match
-// (three waves per SIMD).
+// Three workgroups fill a CU's LDS: registers are bounded to match (three
+// waves per SIMD).
 constexpr int kWavesPerSimd = 3;
 
-// LDS of one workgroup: record staging, thresholds, per-pixel scalars and
+// LDS of one Top-K workgroup: record staging, per-pixel scalars and
 // the merged groups of up to UCAP distinct selections (each pixel's [K]
 // selections live in dynamic LDS).
 template <int UCAP>
-struct QuantileLdsT {
+struct TopkLds {
   static constexpr int kCap = UCAP;
   static constexpr bool kKeepIds = false;  // the walk keeps a staged batch's Gaussian ids (in gid)
   float2 mean[kTilePix];
   float4 co[kTilePix];
-  float thr[QR_MAX_K + 1];
-  double zq[QR_MAX_K];                     // Stratified-K: z_m, m = 1..K
   float inv[kTilePix];
   int ns[kTilePix];
   int unum[kGroups];                       // distinct entries per group, -1 if over UCAP
@@ -60,7 +60,35 @@ struct QuantileLdsT {
   float4 uw[kGroups * UCAP];               // their weights for the group's four pixels, x = first pixel
   uint8_t umask[kGroups * UCAP];           // bit q: pixel q of the group selected the entry
 };
-using QuantileLds = QuantileLdsT<kUCap>;
+
+// LDS of one Q-Render workgroup: record staging, thresholds and the groups'
+// distinct selections as the walk collects them. The size does not depend on
+// K (the pixels' lists took 8 K bytes each and left room for one workgroup per
+// CU at K = 40): three workgroups fit a CU's 160 KB at any K. Groups with
+// more than kGroupCap distinct selections (0.5% of the groups of a room at K =
+// 40, none at K = 8) are collected in further walks of the tile, two groups of
+// a wave at a time in the whole wave's space: kRedoCap = 256 entries each, as
+// many as four pixels can select.
+constexpr int kGroupCap = 32;
+constexpr int kWaveGroups = kGroups / 4;
+constexpr int kRedoGroups = 2;
+constexpr int kRedoCap = kGroupCap * kWaveGroups / kRedoGroups;
+static_assert(kRedoCap >= kPG * QR_MAX_K, "a collected group always fits");
+
+struct QuantileLds {
+  static constexpr bool kKeepIds = true;
+  float2 mean[kTilePix];
+  float4 co[kTilePix];
+  int gid[kTilePix];
+  union {
+    float thr[QR_MAX_K + 1];               // t_1 .. t_K, 0
+    double zq[QR_MAX_K];                   // Stratified-K: z_m, m = 1..K
+  };
+  float4 uw[kGroups * kGroupCap];          // weights of the entries for their group's four pixels
+  int ugid[kGroups * kGroupCap];           // Gaussian ids
+  uint8_t umask[kGroups * kGroupCap];      // bit q: pixel q of the group selected the entry
+};
+static_assert(3 * ((sizeof(QuantileLds) + 64 + 1279) / 1280) * 1280 <= 160 * 1024, "three workgroups per CU");
 
 struct ViewArgs {
   int W, H;
@@ -119,15 +147,88 @@ struct PixelSel {
              // test breaks before T takes the stopping entry's T_test)
   int last;  // Algorithm 1: list position + 1 of the last on-ray entry examined
   int staged;  // list position where the last staged batch of 256 records starts (uniform)
+  float inv;   // 1 / (1 - T^Q) (Top-K: 1 / sum of the kept weights); 0 if nothing was selected
 };
 
+// Each pixel's selections, in list order: absolute positions in sorted_gid
+// and w^Q.
+struct ListSink {
+  int* __restrict__ my_pos;
+  float* __restrict__ my_w;
+  int ns = 0;
+  // sel: lane mask of the pixels that selected list position pos
+  __device__ __forceinline__ void add(uint64_t sel, float w, int pos, int) {
+    if (!__builtin_amdgcn_inverse_ballot_w64(sel)) return;
+    my_pos[ns] = pos;
+    my_w[ns] = w;
+    ++ns;
+  }
+};
+
+// The distinct selections of the lane's group of four pixels. Called with
+// all lanes of the wave (the four lanes of a group count alike).
+struct GroupSink {
+  float* __restrict__ uw;        // the lane's pixel's weight of the group's first entry
+  int* __restrict__ ugid;
+  uint8_t* __restrict__ umask;
+  const int* __restrict__ gid;   // ids of the staged batch
+  int cap;                       // 0: nothing is kept for this group
+  int cnt = 0;
+  int ns = 0;
+  // the pixel's own selections, for callers that ask for them (or null)
+  int32_t* __restrict__ pos_out = nullptr;
+  float* __restrict__ w_out = nullptr;
+  __device__ __forceinline__ void add(uint64_t cross, float w, int pos, int staged) {
+    const int lane = threadIdx.x & 63;
+    const bool sel = __builtin_amdgcn_inverse_ballot_w64(cross);
+    const uint32_t m = static_cast<uint32_t>(cross >> (lane & 60)) & 15u;
+    if (m != 0u) {
+      if (cnt < cap) {
+        uw[kPG * cnt] = sel ? w : 0.f;
+        if ((lane & 3) == 0) {
+          ugid[cnt] = gid[staged];
+          umask[cnt] = static_cast<uint8_t>(m);
+        }
+      }
+      ++cnt;
+    }
+    if (sel) {
+      if (pos_out) {
+        pos_out[ns] = pos;
+        w_out[ns] = w;
+      }
+      ++ns;
+    }
+  }
+};
+
+// Most entries of a list miss all 64 pixels of a wave, so the common path is
+// kept to the evaluation of o G and one wave-uniform branch: the records are
+// staged with 2 b in place of the conic's b (an exact doubling that
+// eval_alpha makes itself), and alpha' = min(alpha_max, o G) is formed only if
+// some pixel has the entry on its ray (o G >= alpha_min). (11 views of 52x196
+// with lists of up to thousands of entries: render 182 -> 156 us; a 64x64
+// picture, one workgroup on a few CUs: 67 -> 62 us.)
+__device__ __forceinline__ float4 staged_conic(f32x4 c) { return make_float4(c.x, c.y + c.y, c.z, c.w); }
+// o G of a staged record, with the float operations of eval_alpha.
+__device__ __forceinline__ float staged_oG(float2 mean, float4 co, float pxc, float pyc) {
+  const float dx = pxc - mean.x, dy = pyc - mean.y;
+  const float cross2 = (co.y * dx) * dy;
+  return co.w * gauss_of(fmaf(co.x * dx, dx, fmaf(co.z * dy, dy, cross2)));
+}
+
+// Lane masks in scalar registers: which pixels of the wave are still walking,
+// have an entry on their ray, cross a threshold. (As per-lane booleans the
+// compiler moves them through vector registers for every wave-uniform branch.)
+__device__ __forceinline__ uint64_t wave_ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+constexpr int kCmpLt = 4, kCmpNotLt = 11;  // a < b; !(a < b)
+
 // The walk for one tile (all 256 threads of the workgroup). Selections go to
-// s_sel_pos / s_sel_w ([256][KP], as absolute positions in sorted_gid and
-// w^Q); L (any LDS struct with the staging arrays mean, co, the thresholds
-// thr and the per-pixel ns, inv) receives ns (-1 outside the image) and
-// 1 / (1 - T^Q). Workgroup barriers occur only around the staging of record
-// batches; the record batch is only rewritten after a barrier that every
-// wave reaches once it has finished the previous tile.
+// `sink`; L (any LDS struct with the staging arrays mean, co and, by rule, the
+// thresholds thr or zq). Workgroup barriers occur only around the staging of
+// record batches; the record batch is only rewritten after a barrier that
+// every wave reaches once it has finished the previous tile.
 // MODE QR_SELECT_QUANTILE: Algorithm 1's thresholds t_m = 1 - m/(K+1).
 // MODE QR_SELECT_STRATIFIED (Stratified-K, Appendix): a first pass over the
 // list estimates the mean and spread of the ray's transmittance values (T_0 =
@@ -137,63 +238,89 @@ struct PixelSel {
 // MODE QR_SELECT_TOPK (the Top-K sampler the paper compares with): the
 // candidates are the Gaussians the dense blend composites (same T_eps stop),
 // each with its dense weight T alpha'; the K largest are kept (equal weights:
-// the earlier position), then put back in list order; 1 / (1 - T^Q) becomes
-// 1 / (sum of the kept weights) and T^Q reports 1 - that sum. A pixel is done
+// the earlier position), then put back in list order, and T^Q reports 1 -
+// their sum (in a ListSink, whose entries it replaces). A pixel is done
 // once its list is full and T alpha_max is no larger than the smallest kept
 // weight: no later weight can exceed it.
-template <int MODE, class WalkLds>
+template <int MODE, class WalkLds, class Sink>
 __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi, int K, float pxc,
                                                   float pyc, bool inside, const qr_params& prm,
-                                                  WalkLds& L, int* __restrict__ s_sel_pos,
-                                                  float* __restrict__ s_sel_w, int KP) {
+                                                  WalkLds& L, Sink& sink) {
   const int tid = threadIdx.x;
   // thr[k] = t_{k+1}; thr[K] = 0 (identical for every tile of a launch)
-  if (MODE == QR_SELECT_QUANTILE && tid <= K) L.thr[tid] = quantile_threshold(tid + 1, K);
+  if constexpr (MODE == QR_SELECT_QUANTILE) {
+    if (tid <= K) L.thr[tid] = quantile_threshold(tid + 1, K);
+  }
   if constexpr (MODE == QR_SELECT_STRATIFIED) {
     if (tid < K) L.zq[tid] = stratified_z(tid + 1, K);  // read after the barrier below
     __syncthreads();
   }
   const float amin = prm.alpha_min, amax = prm.alpha_max;
+  const auto stage = [&](int batch) {
+    const int idx = batch + tid;
+    if (tid >= kTilePix) {
+      // a workgroup wider than the tile: only its first 256 threads walk
+    } else if (idx < hi) {
+      const int g = static_cast<int>(v.sorted_gid[idx]);
+      if constexpr (WalkLds::kKeepIds) L.gid[tid] = g;
+      const f32x2 m = v.means2d[g];
+      const f32x4 c = v.conic_opacity[g];
+      L.mean[tid] = make_float2(m.x, m.y);
+      L.co[tid] = staged_conic(c);
+    } else {  // padding record: opacity 0 is below alpha_min on every ray
+      L.mean[tid] = make_float2(0.f, 0.f);
+      L.co[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __syncthreads();
+  };
+  // kU records are read from LDS and evaluated together (one LDS round trip
+  // and independent arithmetic per group of records; the padding makes every
+  // group whole); touch[u]: pixels with o G >= alpha_min at record u. Returns
+  // the mask of the pixels that any of them touches.
+  constexpr int kU = 8;
+  const auto evaluate = [&](int j, float (&oG)[kU], uint64_t (&touch)[kU]) {
+    float2 rm[kU];
+    float4 rc[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      rm[u] = L.mean[j + u];
+      rc[u] = L.co[j + u];
+    }
+    uint64_t any = 0ull;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) oG[u] = staged_oG(rm[u], rc[u], pxc, pyc);
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      touch[u] = __builtin_amdgcn_fcmpf(oG[u], amin, kCmpNotLt);
+      any |= touch[u];
+    }
+    return any;
+  };
 
   double mu = 0.0, sigma = 0.0;
   if constexpr (MODE == QR_SELECT_STRATIFIED) {
     double s1 = 1.0, s2 = 1.0;  // T_0 = 1
     int n = 1;
     float T1 = 1.f;
-    bool stop = !inside;
+    uint64_t live = wave_ballot(inside);
     for (int batch = lo; batch < hi; batch += kTilePix) {
-      if (__syncthreads_count(!stop) == 0) break;
-      const int idx = batch + tid;
-      if (idx < hi) {
-        const int g = static_cast<int>(v.sorted_gid[idx]);
-        const f32x2 m = v.means2d[g];
-        const f32x4 c = v.conic_opacity[g];
-        L.mean[tid] = make_float2(m.x, m.y);
-        L.co[tid] = make_float4(c.x, c.y, c.z, c.w);
-      } else {  // padding record: opacity 0 is below alpha_min on every ray
-        L.mean[tid] = make_float2(0.f, 0.f);
-        L.co[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      __syncthreads();
-      constexpr int kU = 8;  // records read from LDS per round trip
+      if (__syncthreads_or(live != 0ull) == 0) break;
+      stage(batch);
       const int cnt_pad = (min(kTilePix, hi - batch) + kU - 1) & ~(kU - 1);
       for (int j = 0; j < cnt_pad; j += kU) {
-        if (__all(stop)) break;
-        float2 rm[kU];
-        float4 rc[kU];
+        if (live == 0ull) break;
+        float oG[kU];
+        uint64_t touch[kU];
+        if ((evaluate(j, oG, touch) & live) == 0ull) continue;
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-          rm[u] = L.mean[j + u];
-          rc[u] = L.co[j + u];
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-          const float alpha = gauss_alpha(rm[u], rc[u], pxc, pyc, amax);
-          if (stop || alpha < amin) continue;
+          const uint64_t on = touch[u] & live;
+          if (on == 0ull) continue;
+          const float alpha = oG[u] >= amax ? amax : oG[u];
           const float T_test = T1 * (1.f - alpha);
-          if (T_test < prm.T_eps) {
-            stop = true;
-          } else {
+          const uint64_t stop = __builtin_amdgcn_fcmpf(T_test, prm.T_eps, kCmpLt) & on;
+          live &= ~stop;
+          if (in_mask(on & ~stop)) {
             T1 = T_test;
             s1 += T1;
             s2 += static_cast<double>(T1) * T1;
@@ -207,114 +334,103 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
   }
   auto threshold = [&](int kk) -> float {  // t_{kk+1}; past t_K none is crossed
     if constexpr (MODE == QR_SELECT_STRATIFIED) return kk < K ? stratified_threshold_z(L.zq[kk], mu, sigma) : -1.f;
-    else return L.thr[kk];
+    else if constexpr (MODE == QR_SELECT_QUANTILE) return L.thr[kk];
+    else return -1.f;  // Top-K has none
   };
 
   float T = 1.f, TQ = 1.f;
-  int k = 0, ns = 0, last = 0, staged = lo;
-  bool done = !inside;
+  int k = 0, last = 0, staged = lo;
+  uint64_t live = wave_ballot(inside);  // pixels whose walk has not ended
   // t_{k+1}: changes only at a crossing
   float thr_k;
   if constexpr (MODE == QR_SELECT_STRATIFIED) thr_k = threshold(0);
   else thr_k = quantile_threshold(1, K);
-  int* my_pos = s_sel_pos + tid * KP;
-  float* my_w = s_sel_w + tid * KP;
   float wmin = 0.f;  // Top-K: the worst kept entry (smallest weight, later position among equals)
   int imin = 0;
 
   for (int batch = lo; batch < hi; batch += kTilePix) {
-    if (__syncthreads_count(!done) == 0) break;
+    if (__syncthreads_or(live != 0ull) == 0) break;
     staged = batch;
-    const int idx = batch + tid;
-    if (tid >= kTilePix) {
-      // a workgroup wider than the tile: only its first 256 threads walk
-    } else if (idx < hi) {
-      const int g = static_cast<int>(v.sorted_gid[idx]);
-      if constexpr (WalkLds::kKeepIds) L.gid[tid] = g;
-      const f32x2 m = v.means2d[g];
-      const f32x4 c = v.conic_opacity[g];
-      L.mean[tid] = make_float2(m.x, m.y);
-      L.co[tid] = make_float4(c.x, c.y, c.z, c.w);
-    } else {  // padding record: opacity 0 is below alpha_min on every ray
-      L.mean[tid] = make_float2(0.f, 0.f);
-      L.co[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    __syncthreads();
-    // kWalkUnroll records are read from LDS before any is used (one LDS round
-    // trip per group of records; the padding makes every group whole)
-    constexpr int kWalkUnroll = 8;
-    const int cnt_pad = (min(kTilePix, hi - batch) + kWalkUnroll - 1) & ~(kWalkUnroll - 1);
-    for (int j = 0; j < cnt_pad; j += kWalkUnroll) {
-      if (__all(done)) break;
-      float2 rm[kWalkUnroll];
-      float4 rc[kWalkUnroll];
+    stage(batch);
+    const int cnt_pad = (min(kTilePix, hi - batch) + kU - 1) & ~(kU - 1);
+    for (int j = 0; j < cnt_pad; j += kU) {
+      if (live == 0ull) break;
+      float oG[kU];
+      uint64_t touch[kU];
+      if ((evaluate(j, oG, touch) & live) == 0ull) continue;
 #pragma unroll
-      for (int u = 0; u < kWalkUnroll; ++u) {
-        rm[u] = L.mean[j + u];
-        rc[u] = L.co[j + u];
-      }
-#pragma unroll
-      for (int u = 0; u < kWalkUnroll; ++u) {
-        const float alpha = gauss_alpha(rm[u], rc[u], pxc, pyc, amax);
-        if (done || alpha < amin) continue;  // finished, or not on this pixel's ray
+      for (int u = 0; u < kU; ++u) {
+        uint64_t on = touch[u] & live;  // not finished, and on this pixel's ray
+        if (on == 0ull) continue;
+        const float alpha = oG[u] >= amax ? amax : oG[u];
         const float T_test = T * (1.f - alpha);
+        const int pos = batch + j + u;
+        if constexpr (MODE != QR_SELECT_QUANTILE) {  // the dense blend stops before this Gaussian
+          const uint64_t stop = __builtin_amdgcn_fcmpf(T_test, prm.T_eps, kCmpLt) & on;
+          live &= ~stop;
+          on &= ~stop;
+        }
+        bool end = false;  // the pixel's walk ends with this entry
         if constexpr (MODE == QR_SELECT_TOPK) {
-          if (T_test < prm.T_eps) {  // the dense blend stops before this Gaussian
-            done = true;
-            continue;
-          }
+          int* const my_pos = sink.my_pos;
+          float* const my_w = sink.my_w;
+          int& ns = sink.ns;
           const float w = T * alpha;
-          const int pos = batch + j + u;
-          if (ns < K) {
-            my_pos[ns] = pos;
-            my_w[ns] = w;
-            if (ns == 0 || w <= wmin) {
-              wmin = w;
-              imin = ns;
-            }
-            ++ns;
-          } else if (w > wmin) {
-            my_pos[imin] = pos;
-            my_w[imin] = w;
-            int pmin = my_pos[0];
-            wmin = my_w[0];
-            imin = 0;
-            for (int e = 1; e < K; ++e) {
-              const float we = my_w[e];
-              const int pe = my_pos[e];
-              if (we < wmin || (we == wmin && pe > pmin)) {
-                wmin = we;
-                imin = e;
-                pmin = pe;
+          if (in_mask(on)) {
+            if (ns < K) {
+              my_pos[ns] = pos;
+              my_w[ns] = w;
+              if (ns == 0 || w <= wmin) {
+                wmin = w;
+                imin = ns;
+              }
+              ++ns;
+            } else if (w > wmin) {
+              my_pos[imin] = pos;
+              my_w[imin] = w;
+              int pmin = my_pos[0];
+              wmin = my_w[0];
+              imin = 0;
+              for (int e = 1; e < K; ++e) {
+                const float we = my_w[e];
+                const int pe = my_pos[e];
+                if (we < wmin || (we == wmin && pe > pmin)) {
+                  wmin = we;
+                  imin = e;
+                  pmin = pe;
+                }
               }
             }
+            T = T_test;
+            end = ns == K && T * amax <= wmin;
           }
-          T = T_test;
-          if (ns == K && T * amax <= wmin) done = true;
-          continue;
+        } else {
+          // a quantile Gaussian of the pixel
+          const uint64_t cross = __builtin_amdgcn_fcmpf(T_test, thr_k, kCmpLt) & on;
+          if constexpr (MODE == QR_SELECT_QUANTILE) last = in_mask(on) ? pos - lo + 1 : last;
+          T = in_mask(on & ~cross) ? T_test : T;
+          if (cross == 0ull) continue;
+          const float w = TQ * alpha;
+          if (in_mask(cross)) {
+            TQ = TQ * (1.f - alpha);
+            ++k;
+            while (k < K && T_test < threshold(k)) ++k;  // thresholds crossed by the same step
+            thr_k = threshold(k);
+            end = k == K;
+            // Algorithm 1 leaves T at the stopping entry (the stop test comes first)
+            if (MODE != QR_SELECT_QUANTILE || !end) T = T_test;
+          }
+          sink.add(cross, w, pos, j + u);
         }
-        if (MODE == QR_SELECT_STRATIFIED && T_test < prm.T_eps) {  // the sampled ray ends here
-          done = true;
-          continue;
-        }
-        if constexpr (MODE == QR_SELECT_QUANTILE) last = batch + j + u - lo + 1;
-        if (T_test < thr_k) {  // crossing: a quantile Gaussian
-          my_pos[ns] = batch + j + u;
-          my_w[ns] = TQ * alpha;
-          ++ns;
-          TQ = TQ * (1.f - alpha);
-          ++k;
-          while (k < K && T_test < threshold(k)) ++k;  // thresholds crossed by the same step
-          thr_k = threshold(k);
-          if (k == K) done = true;
-        }
-        // Algorithm 1 leaves T at the stopping entry (the stop test comes first)
-        if (MODE != QR_SELECT_QUANTILE || !done) T = T_test;
+        live &= ~wave_ballot(end);
       }
     }
   }
   if constexpr (MODE == QR_SELECT_TOPK) {
     // back to list order (insertion sort of at most K entries), weight sum
+    int* const my_pos = sink.my_pos;
+    float* const my_w = sink.my_w;
+    const int ns = sink.ns;
     for (int a = 1; a < ns; ++a) {
       const int p = my_pos[a];
       const float w = my_w[a];
@@ -330,18 +446,10 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
     float sum = 0.f;
     for (int a = 0; a < ns; ++a) sum += my_w[a];
     TQ = 1.f - sum;
-    L.ns[tid] = inside ? ns : -1;
-    L.inv[tid] = ns > 0 ? 1.f / sum : 0.f;
-    wave_lds_sync();
-    return PixelSel{ns, TQ, T, last, staged};
+    // 1 / sum, of the sum itself
+    return PixelSel{ns, TQ, T, last, staged, ns > 0 ? 1.f / sum : 0.f};
   }
-  if (tid < kTilePix) {
-    L.ns[tid] = inside ? ns : -1;
-    L.inv[tid] = ns > 0 ? 1.f / (1.f - TQ) : 0.f;
-  }
-  wave_lds_sync();
-
-  return PixelSel{ns, TQ, T, last, staged};
+  return PixelSel{sink.ns, TQ, T, last, staged, sink.ns > 0 ? 1.f / (1.f - TQ) : 0.f};
 }
 
 // The merge for one tile (all 256 threads; wave-local), after the walk.
@@ -356,7 +464,6 @@ __device__ __forceinline__ void merge_groups(const GView& v, Lds& L,
   // pixels' selections. Lane l < 16 merges group 16 w + l.
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  constexpr int kWaveGroups = kGroups / 4;
   if (lane < kWaveGroups) {
     const int grp = wave * kWaveGroups + lane;
     const int p0 = grp * kPG;
@@ -416,18 +523,6 @@ __device__ __forceinline__ void merge_groups(const GView& v, Lds& L,
     }
   }
   wave_lds_sync();
-}
-
-// Walk and merge (the forward renderer's selection phase).
-template <int MODE, class Lds>
-__device__ __forceinline__ PixelSel quantile_select(const GView& v, int lo, int hi, int K,
-                                                    float pxc, float pyc, bool inside,
-                                                    const qr_params& prm, Lds& L,
-                                                    int* __restrict__ s_sel_pos,
-                                                    float* __restrict__ s_sel_w, int KP) {
-  const PixelSel sel = quantile_walk<MODE>(v, lo, hi, K, pxc, pyc, inside, prm, L, s_sel_pos, s_sel_w, KP);
-  merge_groups(v, L, s_sel_pos, s_sel_w, KP);
-  return sel;
 }
 
 }  // namespace qr

@@ -41,6 +41,14 @@ __device__ __forceinline__ float stratified_threshold_z(double z, double mu, dou
 // alpha' = min(alpha_max, o exp(power)), power = -(a dx^2 + 2 b dx dy + c dy^2)/2,
 // with every multiply-add written out so that forward and backward kernels
 // evaluate bit-identical values.
+
+// G = exp(-q/2) = 2^(-q log2(e) / 2): one hardware v_exp_f32 (about one ulp;
+// the rounding of the scaled exponent adds |q| 2^-25 relative)
+__device__ __forceinline__ float gauss_of(float q) {
+  constexpr float kNegHalfLog2e = -0.72134752044448170368f;
+  return __builtin_amdgcn_exp2f(q * kNegHalfLog2e);
+}
+
 struct AlphaEval {
   float alpha, G, dx, dy;
   bool clamped;
@@ -53,10 +61,7 @@ __device__ __forceinline__ AlphaEval eval_alpha(float2 mean, float4 co, float px
   r.dy = pyc - mean.y;
   const float cross2 = ((2.f * co.y) * r.dx) * r.dy;  // products only: nothing to contract
   const float q = fmaf(co.x * r.dx, r.dx, fmaf(co.z * r.dy, r.dy, cross2));
-  // G = exp(-q/2) = 2^(-q log2(e) / 2): one hardware v_exp_f32 (about one ulp;
-  // the rounding of the scaled exponent adds |q| 2^-25 relative)
-  constexpr float kNegHalfLog2e = -0.72134752044448170368f;
-  r.G = __builtin_amdgcn_exp2f(q * kNegHalfLog2e);
+  r.G = gauss_of(q);
   const float raw = co.w * r.G;
   r.clamped = raw >= alpha_max;
   r.alpha = r.clamped ? alpha_max : raw;

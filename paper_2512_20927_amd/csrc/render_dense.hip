@@ -51,8 +51,8 @@ constexpr int kStrips = kTile / kStripRows;        // 4 strips per tile
 constexpr int kDB = 32;                            // list entries per batch (MFMA K)
 constexpr int kDQ = kDB / 4;                       // entries each wave walks per batch
 constexpr int kGrpCols = 64;                       // columns of a group (4 MFMA column tiles)
-constexpr int kWaveGroups = 2;                     // groups per wave and pass
-constexpr int kPassCols = 4 * kWaveGroups * kGrpCols;  // 512 columns per pass
+constexpr int kStripGroups = 2;                     // groups per wave and pass
+constexpr int kPassCols = 4 * kStripGroups * kGrpCols;  // 512 columns per pass
 constexpr int kWS = kDB + 8;                       // LDS row stride (bf16) of a pixel's weights
 static_assert(kDB == kWalkBatch && kDQ == kWalkQ, "the strip's batches are the split walk's");
 
@@ -225,18 +225,18 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
   // next iteration.
   for (int c0 = 0; c0 < dim; c0 += kPassCols) {
     // this wave's column groups in the pass: base column and width (0: none)
-    int gbase[kWaveGroups], gw[kWaveGroups];
+    int gbase[kStripGroups], gw[kStripGroups];
 #pragma unroll
-    for (int k = 0; k < kWaveGroups; ++k) {
+    for (int k = 0; k < kStripGroups; ++k) {
       gbase[k] = c0 + (wave + 4 * k) * kGrpCols;
       gw[k] = max(0, min(kGrpCols, dim - gbase[k]));
     }
     float T = 1.f;
     bool done = !inside;
     int ncon = 0;
-    f32x4 acc[kWaveGroups][4][4];
+    f32x4 acc[kStripGroups][4][4];
 #pragma unroll
-    for (int k = 0; k < kWaveGroups; ++k)
+    for (int k = 0; k < kStripGroups; ++k)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -328,7 +328,7 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
       // wave's features (rows permuted within the group), B = the weights of
       // 16 pixels
 #pragma unroll
-      for (int k = 0; k < kWaveGroups; ++k) {
+      for (int k = 0; k < kStripGroups; ++k) {
         if (k == 1 && prefetch) {
           // the next batch's records (their ids, requested before the first
           // group's MFMAs, have arrived)
@@ -339,13 +339,13 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
         bf16x8 ahi[4], alo[4];
         convert_group<DT>(raw, ahi, alo);
         mfma_group<DT>(acc[k], ahi, alo, L.whi, L.wlo, busy, ci, kb);
-        if (k + 1 < kWaveGroups) load_group(k + 1);
+        if (k + 1 < kStripGroups) load_group(k + 1);
       }
     }
 
     if (c0 + kPassCols >= dim) before_stores();
 #pragma unroll
-    for (int k = 0; k < kWaveGroups; ++k)
+    for (int k = 0; k < kStripGroups; ++k)
       if (gw[k] > 0) store_group(v, acc[k], tx, ty, strip, gbase[k], gw[k], dim, ci, kb);
     if (c0 == 0 && wave == 0 && inside) {
       const int pix = py * W + px;

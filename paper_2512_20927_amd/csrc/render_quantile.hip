@@ -1,23 +1,36 @@
 // Quantile Rendering forward (Algorithm 1, Sec. 4.2).
 //
 // One workgroup per 16x16 tile, one thread per pixel (4 wave64s).
-// Phase 1 (selection, quantile_select.h, shared with the backward): the tile's depth-sorted list is staged into LDS in
-// batches of 256 projected records; every pixel walks it front to back with
-// the transmittance chain T_test = T (1 - alpha') and the threshold test
-// T_test < t_{k+1}, recording the <= K selected (Gaussian id, w^Q) pairs in
-// LDS. A pixel is done once all K thresholds are consumed (the paper's stop
-// test T_test < 1/(K+1) is the same event), and the whole workgroup leaves the
-// list as soon as every pixel is done.
-// Phase 2 (gather-blend): pixels are gathered four at a time (a row segment
-// of the tile) with the lanes of a wave spanning the feature dimension. The
-// four pixels' selection lists are first merged into their distinct
-// selections, each carrying the four weights already divided by the pixel's
-// 1 - T^Q, so every distinct feature row is loaded once per group (mostly
-// from L2: neighbouring pixels select the same Gaussians); rows are
-// accumulated in float32 and streamed to the [H, W, D] map with non-temporal
-// stores. The map write is the dominant HBM traffic of the whole pipeline.
+// Phase 1 (selection, quantile_select.h, the walk shared with the backward):
+// the tile's depth-sorted list is staged into LDS in batches of 256 projected
+// records; every pixel walks it front to back with the transmittance chain
+// T_test = T (1 - alpha') and the threshold test T_test < t_{k+1}. A pixel is
+// done once all K thresholds are consumed (the paper's stop test T_test <
+// 1/(K+1) is the same event), and the whole workgroup leaves the list as soon
+// as every pixel is done. The walk leaves, for each group of four adjacent
+// pixels (a row segment of the tile, four neighbouring lanes that look at an
+// entry together), the group's distinct selections with the four weights,
+// which are then divided by the pixel's 1 - T^Q.
+// Phase 2 (gather-blend): pixels are gathered four at a time with the lanes of
+// a wave spanning the feature dimension, so every distinct feature row is
+// loaded once per group (mostly from L2: neighbouring pixels select the same
+// Gaussians); rows are accumulated in float32 and streamed to the [H, W, D]
+// map with non-temporal stores. The map write is the dominant HBM traffic of
+// the whole pipeline.
 // Everything after the walk is wave-local: wave w's pixels (tile rows
 // 4w .. 4w+3) are exactly the pixels of the groups it gathers.
+// Collecting the groups in the walk instead of lists of each pixel's
+// selections that are merged afterwards takes the merge away, and 51 KB of
+// LDS at any K instead of 29 KB + 2 KB x K, with 32 entries a group instead
+// of 16 (past which rows were loaded pixel by pixel): 16 views 640x480x512
+// float32, K = 8: 2,017 -> 1,985 us (5.2 TB/s; the map write bounds it); 4 views
+// 1296x968x512, bf16 table, K = 16: 2,900 -> 2,060 us (10% of the groups select
+// more than 16); one 640x480x512 view at K = 40: 507 -> 235 us; 16 views
+// 640x480x16, K = 8: 584 -> 480 us.
+// The Top-K sampler replaces entries of its pixels' lists until the end of the
+// list, so it keeps those lists and the merge.
+#include <type_traits>
+
 #include "quantile_select.h"
 
 namespace qr {
@@ -74,19 +87,16 @@ __device__ __forceinline__ void store_out4(QR_GLOBAL float* out, int64_t pix, in
   }
 }
 
-// Gather-blend of one 4-pixel group whose distinct selections are merged:
-// out[p] = sum_e (w_pe / (1 - T^Q_p)) f_e (the normalisation is folded into
-// the merged weights). Each lane owns two float4 columns per pass (512
+// Gather-blend of one 4-pixel group (pixels p0 .. p0 + 3 of the tile) with nu
+// distinct selections: out[p] = sum_e (w_pe / (1 - T^Q_p)) f_e (the
+// normalisation is folded into the weights). Each lane owns two float4 columns per pass (512
 // features per pass for the wave); rows are taken four at a time, the last
 // two or one on their own, so no multiply is spent on padding.
-template <int DT, int OT, class Lds>
-__device__ __forceinline__ void gather_group_merged(const GView& v, const Lds& L, int grp,
-                                                    int nu, int tx, int ty, int lane, int dim) {
+template <int DT, int OT>
+__device__ __forceinline__ void gather_group(const GView& v, const int* ug, const float4* uw,
+                                             const uint8_t* um, int p0, int nu, int tx, int ty,
+                                             int lane, int dim) {
   const int dim4 = dim >> 2;
-  const int p0 = grp * kPG;
-  const int* ug = &L.ugid[grp * Lds::kCap];
-  const float4* uw = &L.uw[grp * Lds::kCap];
-  const uint8_t* um = &L.umask[grp * Lds::kCap];
   for (int cb = 0; cb < dim4; cb += 128) {
     const int c0 = cb + lane, c1 = cb + 64 + lane;
     const int l0 = min(c0, dim4 - 1), l1 = min(c1, dim4 - 1);  // in-bounds columns to load
@@ -106,8 +116,8 @@ __device__ __forceinline__ void gather_group_merged(const GView& v, const Lds& L
 #pragma unroll
     for (int q = 0; q < kPG; ++q) {
       const int p = p0 + q;
-      if (L.ns[p] < 0) continue;  // outside the image
       const int gx = tx * kTile + (p % kTile), gy = ty * kTile + (p / kTile);
+      if (gx >= v.W || gy >= v.H) continue;
       const int64_t pix = static_cast<int64_t>(gy) * v.W + gx;
       if (c0 < dim4) store_out4<OT>(v.out, pix, dim, c0, a0[q]);
       if (c1 < dim4) store_out4<OT>(v.out, pix, dim, c1, a1[q]);
@@ -115,67 +125,68 @@ __device__ __forceinline__ void gather_group_merged(const GView& v, const Lds& L
   }
 }
 
-// Gather-blend of all sixteen merged groups of a wave at once, for narrow
+// Gather-blend of all sixteen groups of a wave at once, for narrow
 // rows (dim <= 128): lpg lanes per group (the power of two >= dim / 4, one
-// float4 column each), so 64 / lpg groups are blended side by side, and all
-// kUCap (16) row loads of a lane are requested before the first is used
+// float4 column each), so 64 / lpg groups are blended side by side, and
+// kNarrowRows (16) row loads of a lane are requested before the first is used
 // (slots past a group's distinct count load a row of the group again and are
-// not accumulated). One memory round trip per round instead of one per
-// group. Groups with more than kUCap distinct selections (also under the
-// larger merge capacity) are skipped here.
-template <int DT, int OT, class Lds>
-__device__ __forceinline__ void gather_groups_narrow(const GView& v, const Lds& L, int wave,
-                                                     int tx, int ty, int lane, int dim) {
-  constexpr int kCap = Lds::kCap;
+// not accumulated). One memory round trip per round and 16 rows instead of
+// several per group. ug, uw: the wave's groups, `cap` entries each;
+// count(g): distinct selections of the wave's group g, negative: skip it.
+constexpr int kNarrowRows = 16;
+
+template <int DT, int OT, class Count>
+__device__ __forceinline__ void gather_groups_narrow(const GView& v, const int* ug, const float4* uw, int cap,
+                                                     const Count& count, int wave, int tx, int ty,
+                                                     int lane, int dim) {
   const int dim4 = dim >> 2;
   const int lpg_log = dim4 <= 4 ? 2 : dim4 <= 8 ? 3 : dim4 <= 16 ? 4 : 5;
   const int gpr = 64 >> lpg_log;  // groups per round
   const int c = lane & ((1 << lpg_log) - 1);
   const int cl = min(c, dim4 - 1);  // in-bounds column to load
-  constexpr int kWaveGroups = kGroups / 4;
   for (int r0 = 0; r0 < kWaveGroups; r0 += gpr) {
-    const int grp = wave * kWaveGroups + r0 + (lane >> lpg_log);
-    const int nu_all = L.unum[grp];
-    const int nu = nu_all > kUCap ? -1 : nu_all;  // more than kUCap: the overflow path
+    const int grp = r0 + (lane >> lpg_log);
+    const int nu = count(grp);
     float4 a[kPG];
 #pragma unroll
     for (int q = 0; q < kPG; ++q) a[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (nu > 0) {
-      const int* ug = &L.ugid[grp * kCap];
-      float4 f[kUCap];
+    for (int e0 = 0; __any(e0 < nu); e0 += kNarrowRows) {
+      if (e0 < nu) {
+        float4 f[kNarrowRows];
 #pragma unroll
-      for (int e = 0; e < kUCap; ++e)
-        f[e] = load_feat4_global<DT>(v.feats, v.scale, ug[min(e, nu - 1)], dim, 4 * cl);
+        for (int e = 0; e < kNarrowRows; ++e)
+          f[e] = load_feat4_global<DT>(v.feats, v.scale, ug[grp * cap + min(e0 + e, nu - 1)], dim, 4 * cl);
 #pragma unroll
-      for (int e = 0; e < kUCap; ++e) {
-        if (e < nu) {
-          const float4 w = L.uw[grp * kCap + e];
-          const float ws[kPG] = {w.x, w.y, w.z, w.w};
+        for (int e = 0; e < kNarrowRows; ++e) {
+          if (e0 + e < nu) {
+            const float4 w = uw[grp * cap + e0 + e];
+            const float ws[kPG] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-          for (int q = 0; q < kPG; ++q) {
-            a[q].x += ws[q] * f[e].x;
-            a[q].y += ws[q] * f[e].y;
-            a[q].z += ws[q] * f[e].z;
-            a[q].w += ws[q] * f[e].w;
+            for (int q = 0; q < kPG; ++q) {
+              a[q].x += ws[q] * f[e].x;
+              a[q].y += ws[q] * f[e].y;
+              a[q].z += ws[q] * f[e].z;
+              a[q].w += ws[q] * f[e].w;
+            }
           }
         }
       }
     }
     if (nu >= 0 && c < dim4) {
-      const int p0 = grp * kPG;
+      const int p0 = (wave * kWaveGroups + grp) * kPG;
 #pragma unroll
       for (int q = 0; q < kPG; ++q) {
         const int p = p0 + q;
-        if (L.ns[p] < 0) continue;  // outside the image
         const int gx = tx * kTile + (p % kTile), gy = ty * kTile + (p / kTile);
-        store_out4<OT>(v.out, static_cast<int64_t>(gy) * v.W + gx, dim, c, a[q]);
+        if (gx < v.W && gy < v.H)
+          store_out4<OT>(v.out, static_cast<int64_t>(gy) * v.W + gx, dim, c, a[q]);
       }
     }
   }
 }
 
-// The groups that gather_groups_narrow skipped (more than kUCap distinct
-// selections, or than the merge capacity), with the same lane layout: pixel by pixel, each pixel's
+// Top-K: the groups that gather_groups_narrow skipped (more distinct
+// selections than the merge capacity), with the same lane layout: pixel by pixel, each pixel's
 // selections taken eight at a time (their ids, then their rows, each batch
 // requested together), all such groups of a round side by side.
 template <int DT, int OT, class Lds>
@@ -190,10 +201,9 @@ __device__ __forceinline__ void gather_groups_narrow_overflow(const GView& v, co
   const int gpr = 64 >> lpg_log;
   const int c = lane & ((1 << lpg_log) - 1);
   const int cl = min(c, dim4 - 1);
-  constexpr int kWaveGroups = kGroups / 4;
   for (int r0 = 0; r0 < kWaveGroups; r0 += gpr) {
     const int grp = wave * kWaveGroups + r0 + (lane >> lpg_log);
-    const bool mine = L.unum[grp] < 0 || L.unum[grp] > kUCap;
+    const bool mine = L.unum[grp] < 0;
     if (!__any(mine)) continue;
 #pragma unroll 1
     for (int q = 0; q < kPG; ++q) {
@@ -235,7 +245,7 @@ __device__ __forceinline__ void gather_groups_narrow_overflow(const GView& v, co
   }
 }
 
-// Gather-blend of a group with more distinct selections than the merge
+// Top-K: gather-blend of a group with more distinct selections than the merge
 // capacity: pixel by pixel, each selection's row loaded for its own pixel.
 template <int DT, int OT, class Lds>
 __device__ __forceinline__ void gather_group_per_pixel(const GView& v, const Lds& L,
@@ -288,72 +298,185 @@ __device__ __forceinline__ void gather_group_per_pixel(const GView& v, const Lds
   }
 }
 
-// Algorithm 1 for every pixel of one tile, then the gather-blend of the
-// selected rows. Called by all 256 threads of the workgroup. Workgroup
-// barriers occur only around the staging of record batches; the pixels of
-// wave w are tile rows 4w .. 4w+3, which are exactly the pixels of the
-// gather groups it owns, so everything after the walk is wave-local.
-// Shared LDS (the record batch) is only rewritten after a barrier that every
-// wave reaches once it has finished the previous tile.
-template <int DT, int OT, int MODE, class Lds>
-__device__ __forceinline__ void quantile_tile(const GView& v, int tile, int K, int dim,
-                                              const qr_params& prm, Lds& L,
-                                              int* __restrict__ s_sel_gid,
-                                              float* __restrict__ s_sel_w,
-                                              int32_t* __restrict__ sel_gid_out,
-                                              float* __restrict__ sel_w_out,
-                                              float* __restrict__ T_final_out,
-                                              int32_t* __restrict__ last_pos_out) {
-  const int W = v.W, H = v.H;
-  const int tiles_x = (W + kTile - 1) / kTile;
-  const int tid = threadIdx.x;
-  const int tx = tile % tiles_x, ty = tile / tiles_x;
-  const int px = tx * kTile + (tid % kTile);
-  const int py = ty * kTile + (tid / kTile);
-  const bool inside = px < W && py < H;
-  const float pxc = px + 0.5f, pyc = py + 0.5f;
+// A tile's place and the calling thread's pixel.
+struct TilePixel {
+  int tx, ty, px, py;
+  bool inside;
+  __device__ TilePixel(const GView& v, int tile) {
+    const int tiles_x = (v.W + kTile - 1) / kTile;
+    tx = tile % tiles_x;
+    ty = tile / tiles_x;
+    px = tx * kTile + static_cast<int>(threadIdx.x % kTile);
+    py = ty * kTile + static_cast<int>(threadIdx.x / kTile);
+    inside = px < v.W && py < v.H;
+  }
+};
 
-  const int lo = static_cast<int>(v.tile_offsets[tile]);
-  const int hi = static_cast<int>(v.tile_offsets[tile + 1]);
+// Top-K for every pixel of one tile: walk, merge, gather-blend. Called by all
+// 256 threads of the workgroup. K selections of each pixel in LDS.
+template <int DT, int OT, int UCAP>
+__device__ __forceinline__ void topk_tile(const GView& v, int tile, int K, int dim, const qr_params& prm,
+                                          TopkLds<UCAP>& L, unsigned char* __restrict__ dyn_lds,
+                                          int32_t* __restrict__ sel_gid_out, float* __restrict__ sel_w_out) {
+  const int tid = threadIdx.x;
+  const TilePixel t(v, tile);
+  const int tx = t.tx, ty = t.ty;
   const int KP = (K + 3) & ~3;  // selection row stride: 16-byte aligned rows
-  int* s_sel_pos = s_sel_gid;   // selections are kept as tile-list positions
-  const PixelSel sel = quantile_select<MODE>(v, lo, hi, K, pxc, pyc, inside, prm, L, s_sel_pos, s_sel_w, KP);
-  const int ns = sel.ns;
-  const float TQ = sel.TQ;
-  const int* my_pos = s_sel_pos + tid * KP;
-  const float* my_w = s_sel_w + tid * KP;
+  int* const s_sel_pos = reinterpret_cast<int*>(dyn_lds);                 // [256][KP], tile-list positions
+  float* const s_sel_w = reinterpret_cast<float*>(dyn_lds) + kTilePix * KP;  // [256][KP]
+  ListSink sink{s_sel_pos + tid * KP, s_sel_w + tid * KP};
+  const PixelSel sel = quantile_walk<QR_SELECT_TOPK>(v, static_cast<int>(v.tile_offsets[tile]),
+                                                     static_cast<int>(v.tile_offsets[tile + 1]), K, t.px + 0.5f,
+                                                     t.py + 0.5f, t.inside, prm, L, sink);
+  L.ns[tid] = t.inside ? sel.ns : -1;
+  L.inv[tid] = sel.inv;
+  wave_lds_sync();
+  merge_groups(v, L, s_sel_pos, s_sel_w, KP);
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  constexpr int kWaveGroups = kGroups / 4;
+  const int g0 = wave * kWaveGroups;
   if (dim <= 128) {
-    gather_groups_narrow<DT, OT>(v, L, wave, tx, ty, lane, dim);
+    gather_groups_narrow<DT, OT>(v, &L.ugid[g0 * UCAP], &L.uw[g0 * UCAP], UCAP,
+                                 [&](int g) { return L.unum[g0 + g]; }, wave, tx, ty, lane, dim);
     gather_groups_narrow_overflow<DT, OT>(v, L, s_sel_pos, s_sel_w, KP, K, wave, tx, ty, lane, dim);
   } else {
     for (int gl = 0; gl < kWaveGroups; ++gl) {
-      const int grp = wave * kWaveGroups + gl;
+      const int grp = g0 + gl;
       const int nu = __builtin_amdgcn_readfirstlane(L.unum[grp]);
       if (nu >= 0)
-        gather_group_merged<DT, OT>(v, L, grp, nu, tx, ty, lane, dim);
+        gather_group<DT, OT>(v, &L.ugid[grp * UCAP], &L.uw[grp * UCAP], &L.umask[grp * UCAP], grp * kPG, nu,
+                             tx, ty, lane, dim);
       else  // more distinct selections than the merge capacity (rare)
         gather_group_per_pixel<DT, OT>(v, L, s_sel_pos, s_sel_w, KP, grp, tx, ty, lane, dim);
     }
   }
   // Per-pixel outputs last: a load issued after a store waits for it, so no
   // store precedes the loads of the merge and the gather.
-  if (inside) {
-    const int pix = py * W + px;
-    if (v.T_q) v.T_q[pix] = TQ;
-    if (v.n_sel) v.n_sel[pix] = ns;
-    if (T_final_out) T_final_out[pix] = sel.T;
-    if (last_pos_out) last_pos_out[pix] = sel.last;
+  if (t.inside) {
+    const int pix = t.py * v.W + t.px;
+    if (v.T_q) v.T_q[pix] = sel.TQ;
+    if (v.n_sel) v.n_sel[pix] = sel.ns;
     if (sel_gid_out) {
       for (int j = 0; j < K; ++j) {
         sel_gid_out[static_cast<int64_t>(pix) * K + j] =
-            j < ns ? static_cast<int>(v.sorted_gid[my_pos[j]]) : -1;
-        sel_w_out[static_cast<int64_t>(pix) * K + j] = j < ns ? my_w[j] : 0.f;
+            j < sel.ns ? static_cast<int>(v.sorted_gid[sink.my_pos[j]]) : -1;
+        sel_w_out[static_cast<int64_t>(pix) * K + j] = j < sel.ns ? sink.my_w[j] : 0.f;
       }
     }
   }
+}
+
+// Algorithm 1 (or Stratified-K) for every pixel of one tile, then the
+// gather-blend of the selected rows. Called by all 256 threads of the
+// workgroup. Workgroup barriers occur only around the staging of record
+// batches; everything after the walk is wave-local. Shared LDS (the record
+// batch) is only rewritten after a barrier that every wave reaches once it has
+// finished the previous tile.
+template <int DT, int OT, int MODE>
+__device__ __forceinline__ void quantile_tile(const GView& v, int tile, int K, int dim,
+                                              const qr_params& prm, QuantileLds& L,
+                                              int32_t* __restrict__ sel_gid_out,
+                                              float* __restrict__ sel_w_out,
+                                              float* __restrict__ T_final_out,
+                                              int32_t* __restrict__ last_pos_out) {
+  const int tid = threadIdx.x;
+  const TilePixel t(v, tile);
+  const int tx = t.tx, ty = t.ty;
+  const float pxc = t.px + 0.5f, pyc = t.py + 0.5f;
+  const int lo = static_cast<int>(v.tile_offsets[tile]);
+  const int hi = static_cast<int>(v.tile_offsets[tile + 1]);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the wave's entries, and the lane's group among its sixteen
+  constexpr int kWaveCap = kWaveGroups * kGroupCap;
+  float4* const uw = L.uw + wave * kWaveCap;
+  int* const ug = L.ugid + wave * kWaveCap;
+  uint8_t* const um = L.umask + wave * kWaveCap;
+  const int lg = lane >> 2, q = lane & 3;
+  const auto collect = [&](bool on, int first, int cap, bool outputs, int& cnt) {
+    GroupSink sink{reinterpret_cast<float*>(uw + first) + q, ug + first, um + first, L.gid, cap};
+    if (outputs) {
+      const int64_t at = static_cast<int64_t>(t.py * v.W + t.px) * K;
+      sink.pos_out = sel_gid_out + at;
+      sink.w_out = sel_w_out + at;
+    }
+    const PixelSel sel = quantile_walk<MODE>(v, lo, hi, K, pxc, pyc, on, prm, L, sink);
+    cnt = sink.cnt;
+    // the weights over 1 - T^Q, each lane its pixel's
+    for (int e = 0; e < min(cnt, cap); ++e) sink.uw[kPG * e] *= sel.inv;
+    wave_lds_sync();
+    return sel;
+  };
+  int cnt;
+  const PixelSel sel = collect(t.inside, lg * kGroupCap, kGroupCap, t.inside && sel_gid_out, cnt);
+  if (dim <= 128) {
+    gather_groups_narrow<DT, OT>(v, ug, uw, kGroupCap,
+                                 [&](int g) {
+                                   const int n = __shfl(cnt, 4 * g, 64);
+                                   return n > kGroupCap ? -1 : n;
+                                 },
+                                 wave, tx, ty, lane, dim);
+  } else {
+    for (int g = 0; g < kWaveGroups; ++g) {
+      const int nu = __builtin_amdgcn_readlane(cnt, 4 * g);
+      if (nu <= kGroupCap)
+        gather_group<DT, OT>(v, ug + g * kGroupCap, uw + g * kGroupCap, um + g * kGroupCap,
+                             (wave * kWaveGroups + g) * kPG, nu, tx, ty, lane, dim);
+    }
+  }
+  if (kPG * K > kGroupCap) {
+    // groups past the capacity, kRedoGroups of a wave per further walk
+    uint64_t redo = __ballot(cnt > kGroupCap) & 0x1111111111111111ull;
+    while (__syncthreads_or(redo != 0ull)) {
+      const int g0 = redo ? __builtin_ctzll(redo) >> 2 : -1;
+      redo &= redo - 1ull;
+      const int g1 = redo ? __builtin_ctzll(redo) >> 2 : -1;
+      redo &= redo - 1ull;
+      const bool mine = lg == g0 || lg == g1;
+      int n;
+      collect(t.inside && mine, lg == g1 ? kRedoCap : 0, mine ? kRedoCap : 0, false, n);
+      for (int k = 0; k < kRedoGroups; ++k) {
+        const int g = k ? g1 : g0;
+        if (g >= 0)
+          gather_group<DT, OT>(v, ug + k * kRedoCap, uw + k * kRedoCap, um + k * kRedoCap,
+                               (wave * kWaveGroups + g) * kPG, __builtin_amdgcn_readlane(n, 4 * g), tx, ty,
+                               lane, dim);
+      }
+    }
+  }
+  // Per-pixel outputs last: a load issued after a store waits for it, so no
+  // store precedes the loads of the gather.
+  if (t.inside) {
+    const int pix = t.py * v.W + t.px;
+    if (v.T_q) v.T_q[pix] = sel.TQ;
+    if (v.n_sel) v.n_sel[pix] = sel.ns;
+    if (T_final_out) T_final_out[pix] = sel.T;
+    if (last_pos_out) last_pos_out[pix] = sel.last;
+    if (sel_gid_out) {
+      // the walk has left list positions and weights
+      for (int j = 0; j < K; ++j) {
+        const int64_t at = static_cast<int64_t>(pix) * K + j;
+        sel_gid_out[at] = j < sel.ns ? static_cast<int>(v.sorted_gid[sel_gid_out[at]]) : -1;
+        if (j >= sel.ns) sel_w_out[at] = 0.f;
+      }
+    }
+  }
+}
+
+// LDS and tile function by selection rule. (UCAP: Top-K's merge capacity, 16
+// for the other rules.)
+template <int MODE, int UCAP>
+using TileLds = std::conditional_t<MODE == QR_SELECT_TOPK, TopkLds<UCAP>, QuantileLds>;
+
+template <int DT, int OT, int MODE, int UCAP>
+__device__ __forceinline__ void render_tile(const GView& v, int tile, int K, int dim, const qr_params& prm,
+                                            TileLds<MODE, UCAP>& L, unsigned char* __restrict__ dyn_lds,
+                                            int32_t* __restrict__ sel_gid_out, float* __restrict__ sel_w_out,
+                                            float* __restrict__ T_final_out, int32_t* __restrict__ last_pos_out) {
+  if constexpr (MODE == QR_SELECT_TOPK)
+    topk_tile<DT, OT, UCAP>(v, tile, K, dim, prm, L, dyn_lds, sel_gid_out, sel_w_out);
+  else
+    quantile_tile<DT, OT, MODE>(v, tile, K, dim, prm, L, sel_gid_out, sel_w_out, T_final_out, last_pos_out);
 }
 
 template <int DT, int OT, int MODE, int UCAP>
@@ -362,11 +485,9 @@ render_quantile_kernel(ViewArgs v, int n_tiles, qr_params prm, int K, int dim,
                        int32_t* __restrict__ sel_gid_out, float* __restrict__ sel_w_out,
                        float* __restrict__ T_final_out, int32_t* __restrict__ last_pos_out) {
   extern __shared__ unsigned char dyn_lds[];
-  __shared__ QuantileLdsT<UCAP> L;
-  int* s_sel_gid = reinterpret_cast<int*>(dyn_lds);                            // [256][KP]
-  float* s_sel_w = reinterpret_cast<float*>(dyn_lds) + kTilePix * ((K + 3) & ~3);  // [256][KP]
-  quantile_tile<DT, OT, MODE>(to_global(v), xcd_remap(blockIdx.x, n_tiles), K, dim, prm, L, s_sel_gid,
-                    s_sel_w, sel_gid_out, sel_w_out, T_final_out, last_pos_out);
+  __shared__ TileLds<MODE, UCAP> L;
+  render_tile<DT, OT, MODE, UCAP>(to_global(v), xcd_remap(blockIdx.x, n_tiles), K, dim, prm, L, dyn_lds,
+                                  sel_gid_out, sel_w_out, T_final_out, last_pos_out);
 }
 
 // Many views in one persistent launch. The schedule is cut into one
@@ -387,10 +508,8 @@ render_quantile_batched_kernel(const qr_view* __restrict__ views, const uint32_t
                                int64_t n_items, uint32_t* __restrict__ counter, qr_params prm,
                                int K, int dim) {
   extern __shared__ unsigned char dyn_lds[];
-  __shared__ QuantileLdsT<UCAP> L;
+  __shared__ TileLds<MODE, UCAP> L;
   __shared__ uint32_t s_item[2];
-  int* s_sel_gid = reinterpret_cast<int*>(dyn_lds);
-  float* s_sel_w = reinterpret_cast<float*>(dyn_lds) + kTilePix * ((K + 3) & ~3);
   // The item slot alternates between two words: a wave that runs ahead into
   // the next iteration writes the other word, and cannot come back to this
   // one before every wave has passed the next barrier (and so has read it).
@@ -416,8 +535,8 @@ render_quantile_batched_kernel(const qr_view* __restrict__ views, const uint32_t
     if (item >= n_items) break;
     const uint32_t packed = __builtin_amdgcn_readfirstlane(schedule[item]);
     const GView v = to_global(view_args(views[packed >> kViewShift]));
-    quantile_tile<DT, OT, MODE>(v, static_cast<int>(packed & kTileMask), K, dim, prm, L, s_sel_gid, s_sel_w,
-                      nullptr, nullptr, nullptr, nullptr);
+    render_tile<DT, OT, MODE, UCAP>(v, static_cast<int>(packed & kTileMask), K, dim, prm, L, dyn_lds, nullptr,
+                                    nullptr, nullptr, nullptr);
   }
 }
 
@@ -431,13 +550,11 @@ render_quantile_batched_grid_kernel(const qr_view* __restrict__ views,
                                     const uint32_t* __restrict__ schedule, int n_items,
                                     qr_params prm, int K, int dim) {
   extern __shared__ unsigned char dyn_lds[];
-  __shared__ QuantileLdsT<UCAP> L;
-  int* s_sel_gid = reinterpret_cast<int*>(dyn_lds);
-  float* s_sel_w = reinterpret_cast<float*>(dyn_lds) + kTilePix * ((K + 3) & ~3);
+  __shared__ TileLds<MODE, UCAP> L;
   const uint32_t packed = __builtin_amdgcn_readfirstlane(schedule[xcd_remap(blockIdx.x, n_items)]);
   const GView v = to_global(view_args(views[packed >> kViewShift]));
-  quantile_tile<DT, OT, MODE>(v, static_cast<int>(packed & kTileMask), K, dim, prm, L, s_sel_gid, s_sel_w,
-                    nullptr, nullptr, nullptr, nullptr);
+  render_tile<DT, OT, MODE, UCAP>(v, static_cast<int>(packed & kTileMask), K, dim, prm, L, dyn_lds, nullptr,
+                                  nullptr, nullptr, nullptr);
 }
 
 __global__ void reset_counter_kernel(uint32_t* __restrict__ c) {
@@ -449,7 +566,7 @@ __global__ void reset_counter_kernel(uint32_t* __restrict__ c) {
 using namespace qr;
 
 // Instantiates QR_LAUNCH(feature dtype, output dtype, selection rule, merge
-// capacity) for the runtime values; the larger merge capacity is built for
+// capacity) for the runtime values; Top-K's larger merge capacity is built for
 // float32 maps (bfloat16 maps keep 16, which is correct at any K).
 #define QR_DISPATCH_DT(dt, OT, SM, UC)                        \
   switch (dt) {                                               \
@@ -457,18 +574,31 @@ using namespace qr;
     case QR_BF16: QR_LAUNCH(QR_BF16, OT, SM, UC); break;      \
     default: QR_LAUNCH(QR_FP8_E4M3, OT, SM, UC); break;       \
   }
-#define QR_DISPATCH_OT(dt, ot, SM, K)                                                   \
-  do {                                                                                  \
-    if ((ot) == QR_BF16) { QR_DISPATCH_DT(dt, QR_BF16, SM, kUCap) }                     \
-    else if (ucap_for(K) == kUCapLarge) { QR_DISPATCH_DT(dt, QR_F32, SM, kUCapLarge) }  \
-    else { QR_DISPATCH_DT(dt, QR_F32, SM, kUCap) }                                      \
+#define QR_DISPATCH_OT(dt, ot, SM)                            \
+  do {                                                        \
+    if ((ot) == QR_BF16) { QR_DISPATCH_DT(dt, QR_BF16, SM, kUCap) } \
+    else { QR_DISPATCH_DT(dt, QR_F32, SM, kUCap) }            \
   } while (0)
-#define QR_DISPATCH(dt, ot, sm, K)                                                  \
-  do {                                                                              \
-    if ((sm) == QR_SELECT_TOPK) QR_DISPATCH_OT(dt, ot, QR_SELECT_TOPK, K);          \
-    else if ((sm) == QR_SELECT_STRATIFIED) QR_DISPATCH_OT(dt, ot, QR_SELECT_STRATIFIED, K); \
-    else QR_DISPATCH_OT(dt, ot, QR_SELECT_QUANTILE, K);                             \
+#define QR_DISPATCH(dt, ot, sm, K)                                                          \
+  do {                                                                                      \
+    if ((sm) == QR_SELECT_TOPK) {                                                           \
+      if ((ot) != QR_BF16 && ucap_for(K) == kUCapLarge) {                                   \
+        QR_DISPATCH_DT(dt, QR_F32, QR_SELECT_TOPK, kUCapLarge)                              \
+      } else {                                                                              \
+        QR_DISPATCH_OT(dt, ot, QR_SELECT_TOPK);                                             \
+      }                                                                                     \
+    } else if ((sm) == QR_SELECT_STRATIFIED) {                                              \
+      QR_DISPATCH_OT(dt, ot, QR_SELECT_STRATIFIED);                                         \
+    } else {                                                                                \
+      QR_DISPATCH_OT(dt, ot, QR_SELECT_QUANTILE);                                           \
+    }                                                                                       \
   } while (0)
+
+// Dynamic LDS: Top-K's selection lists.
+static size_t list_bytes(int32_t selection, int32_t K) {
+  return selection == QR_SELECT_TOPK ? static_cast<size_t>(kTilePix) * ((K + 3) & ~3) * (sizeof(int) + sizeof(float))
+                                     : 0;
+}
 
 extern "C" int qr_render_quantile(void* stream, int32_t width, int32_t height,
                                   const qr_params* prm, int32_t K, const uint32_t* tile_offsets,
@@ -491,7 +621,7 @@ extern "C" int qr_render_quantile(void* stream, int32_t width, int32_t height,
   const int tiles_y = static_cast<int>(ceil_div(height, kTile));
   const int n_tiles = tiles_x * tiles_y;
   (void)tiles_x;
-  const size_t lds = static_cast<size_t>(kTilePix) * ((K + 3) & ~3) * (sizeof(int) + sizeof(float));
+  const size_t lds = list_bytes(prm->selection, K);
   hipStream_t s = as_stream(stream);
   const ViewArgs v{width, height, tile_offsets, sorted_gid, reinterpret_cast<const float2*>(means2d),
                    reinterpret_cast<const float4*>(conic_opacity), features, feature_scale, out, T_q,
@@ -534,7 +664,7 @@ extern "C" int qr_render_quantile_batched(void* stream, int32_t n_views, const q
     return fail(QR_ERR_UNSUPPORTED, "qr_render_quantile_batched: unknown selection rule %d", prm->selection);
   if (n_items == 0) return QR_OK;
   hipStream_t s = as_stream(stream);
-  const size_t lds = static_cast<size_t>(kTilePix) * ((K + 3) & ~3) * (sizeof(int) + sizeof(float));
+  const size_t lds = list_bytes(prm->selection, K);
   if (n_workgroups == 0) {
     const int ni = static_cast<int>(n_items);
 #define QR_LAUNCH(DT, OT, SM, UC)                                                                     \

@@ -33,7 +33,8 @@
 //     are the total minus the running prefix, both kept in double.
 // Both products of step 2 take float32 operands split into bfloat16 pairs
 // x = x_hi + x_lo and form hi.hi + hi.lo + lo.hi with float32 accumulation
-// (relative error below 2^-16 per product). Selections without a slot (more
+// (relative error below 2^-16 per product; three parts past a tile's first 32
+// slots). Selections without a slot (more
 // than 256 distinct selections in a tile, or a position past kPosCap) are
 // handled by a plain wave-wide path.
 //
@@ -45,6 +46,8 @@
 // on its own, and LDS float atomics for the geometric sums: 500k Gaussians,
 // 640x480x512, bf16, K = 8: 640 -> 280 us; 200k, float32, K = 40: 2,400 -> 505
 // us; 8 views 1280x720, e4m3, K = 8: 7.01 -> 4.1 ms (3.7 TB/s of dL/d(out)).
+#include <type_traits>
+
 #include "quantile_select.h"
 #include "wave_ops.h"
 
@@ -93,7 +96,7 @@ __device__ __forceinline__ void load_feat8(const GView& v, int64_t g, int dim, i
   f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
 }
 
-constexpr int kSlots = 32;       // distinct selections of one pass over dL/d(out)
+constexpr int kSlots = 32;       // distinct selections of one pass over dL/d(out) (at most)
 constexpr int kMaxSlots = 256;   // distinct selections of a tile given slots
 constexpr int kPosCap = 8192;    // list positions covered by the slot bitmap
 constexpr int kPosWords = kPosCap / 32;
@@ -120,7 +123,6 @@ struct BwdLds {
   __attribute__((aligned(16))) unsigned char stage[kStage];
   float thr[QR_MAX_K + 1];
   __attribute__((aligned(16))) float inv[kTilePix];
-  int ns[kTilePix];
   __attribute__((aligned(16))) uint32_t smask[kTilePix];  // per pixel: slots of the pass it selected
   __attribute__((aligned(16))) int sj[kTilePix];          // place of the first of them in the lists
   uint32_t bm[kPosWords];   // selected positions, relative to the list start
@@ -136,14 +138,12 @@ struct BwdWalkLds {
   float2* mean;
   float4* co;
   float* thr;
-  float* inv;
-  int* ns;
   int* gid;
   static constexpr bool kKeepIds = true;
   __device__ explicit BwdWalkLds(BwdLds<NW>& B)
       : mean(reinterpret_cast<typename BwdLds<NW>::Stage*>(B.stage)->mean),
         co(reinterpret_cast<typename BwdLds<NW>::Stage*>(B.stage)->co),
-        thr(B.thr), inv(B.inv), ns(B.ns), gid(reinterpret_cast<typename BwdLds<NW>::Stage*>(B.stage)->gid) {}
+        thr(B.thr), gid(reinterpret_cast<typename BwdLds<NW>::Stage*>(B.stage)->gid) {}
 };
 
 // Four bf16 of an LDS tile, transposed over each 16 lanes: with lane 4e + g
@@ -231,21 +231,32 @@ struct Shares {
 // tiles and the workgroup adds them up for the selected pairs, one thread per
 // (pixel, selection). (Adding them with LDS float atomics kept the LDS busy
 // for 61% of the kernel.)
-template <int DT, int NW, bool DF, bool DOT>
+// FAR: the passes after the first. float32 operands are split into three
+// bfloat16 parts instead of two, six products instead of three, which keeps
+// float32's precision (relative error 2^-24 instead of 2^-16; a tile's later
+// selections were always taken in float32), and half the slots are taken per
+// pass, as the parts take the registers of the other half (with 32 slots they
+// spill: 495 against 397 us for a picture whose tiles select 70).
+template <bool FAR>
+constexpr int pass_slots() { return FAR ? kSlots / 2 : kSlots; }
+
+template <int DT, int NW, bool DF, bool DOT, bool FAR>
 __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, BwdLds<NW>& B,
                                              float* __restrict__ s_w, int base, int nslot, bool add,
                                              const Shares<NW>& sh, f32x4 (&raw)[Shares<NW>::kBuf][4],
                                              int wave, int lane, int dim) {
   using Sh = Shares<NW>;
   constexpr int MS = Sh::MS, kBuf = Sh::kBuf, kBlocks = Sh::kBlocks;
-  constexpr int MB = kSlots / 16;
+  constexpr int MB = pass_slots<FAR>() / 16;
+  constexpr int P = FAR ? 3 : 2;              // parts of a float32 operand
+  constexpr int PF = DT == QR_F32 ? P : 1;    // of a feature (bf16 features and e4m3 codes are exact in one)
   const int row = lane & 15, kb = lane >> 4;
   const int n_mb = (nslot + 15) >> 4;  // blocks of 16 slots (uniform)
   const int n_sc = sh.n_sc, cgroups = sh.cgroups, pgroups = sh.pgroups, pg = sh.pg, sub0 = sh.sub0, nsub = sh.nsub;
   const bool partial = (dim & (kSub - 1)) != 0;  // the last block is half a block
 
   // B operand of D: feature rows of the slots, this wave's columns
-  bf16x8 fhi[MS][MB], flo[MS][MB];
+  bf16x8 fp[MS][MB][PF];
   if constexpr (DOT) {
 #pragma unroll
     for (int s = 0; s < MS; ++s) {
@@ -259,7 +270,7 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
 #pragma unroll
             for (int i = 0; i < 8; ++i) x[i] = 0.f;
           }
-          split8(x, fhi[s][nb], flo[s][nb]);
+          split_parts<PF>(x, fp[s][nb]);
         }
       }
     }
@@ -274,18 +285,28 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
         for (int mb = 0; mb < MB; ++mb) af[s][cb][mb] = floatx4{0.f, 0.f, 0.f, 0.f};
   }
 
-  __bf16* const thi = reinterpret_cast<__bf16*>(B.stage + wave * BwdLds<NW>::kTileBytes);
-  __bf16* const tlo = thi + kPB * kTS;
+  // the wave's transposing tile: two parts of a block
+  __bf16* const tile0 = reinterpret_cast<__bf16*>(B.stage + wave * BwdLds<NW>::kTileBytes);
   const int t_wr = row * kTS + 8 * kb;                         // + 16 rows for the second pixel row
   const int t_rd = (8 * kb + (row >> 2)) * kTS + 4 * (row & 3);  // + 4 rows, + 16 columns
+  const auto put = [&](int area, const bf16x8& r0, const bf16x8& r1) {
+    __bf16* const t = tile0 + area * (kPB * kTS) + t_wr;
+    *reinterpret_cast<bf16x8*>(t) = r0;
+    *reinterpret_cast<bf16x8*>(t + 16 * kTS) = r1;
+  };
+  const auto get = [&](int area, int cb) {  // eight pixels of a column
+    const __bf16* const t = tile0 + area * (kPB * kTS) + t_rd + 16 * cb;
+    return __builtin_shufflevector(lds_read_tr(t), lds_read_tr(t + 4 * kTS), 0, 1, 2, 3, 4, 5, 6, 7);
+  };
 
 #pragma unroll 1
   for (int pb = 0; pb < kBlocks; ++pb) {
-    if (pb % pgroups == pg && nsub > 0) {
+    const bool mine = pb % pgroups == pg && nsub > 0;  // uniform
+    if (mine) {
       const int pb_next = pb + pgroups < kBlocks ? pb + pgroups : pb;
       // A operand of dF: w / Z of slot mb * 16 + row, pixels 8 kb .. 8 kb + 7
       // of the block
-      bf16x8 whi[MB], wlo[MB];
+      bf16x8 wp[MB][P];
       if constexpr (DF) {
         const int p0 = pb * kPB + 8 * kb;
         float w[MB][8];
@@ -303,7 +324,7 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
           }
         }
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) split8(w[mb], whi[mb], wlo[mb]);
+        for (int mb = 0; mb < MB; ++mb) split_parts<P>(w[mb], wp[mb]);
       }
       floatx4 ad[2][MB];
       if constexpr (DOT) {
@@ -315,7 +336,7 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
 #pragma unroll
       for (int s = 0; s < MS; ++s) {
         f32x4(&x)[4] = raw[s % kBuf];
-        bf16x8 ahi[2], alo[2];
+        bf16x8 ap[2][P];  // the block's two pixel rows
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
           float y[8];
@@ -324,24 +345,23 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
             y[i] = x[2 * rb][i];
             y[4 + i] = x[2 * rb + 1][i];
           }
-          split8(y, ahi[rb], alo[rb]);
+          split_parts<P>(y, ap[rb]);
         }
         if (partial && (sub0 + s) * kSub + 8 * kb >= dim) {  // columns past dim
 #pragma unroll
-          for (int rb = 0; rb < 2; ++rb) ahi[rb] = alo[rb] = bf16x8{};
+          for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int i = 0; i < P; ++i) ap[rb][i] = bf16x8{};
         }
         // the block two steps on, into the registers just read (always a
-        // load, at the end of one of this pass's blocks again: under a
+        // load, at the end one of this pass's blocks again: under a
         // condition the compiler waits for it on the spot)
         if (s + kBuf < MS) sh.load(pb, s + kBuf, x);
         else sh.load(pb_next, s + kBuf - MS, x);
         if (s >= nsub) continue;  // uniform
         if constexpr (DF) {
-#pragma unroll
-          for (int rb = 0; rb < 2; ++rb) {
-            *reinterpret_cast<bf16x8*>(&thi[t_wr + 16 * rb * kTS]) = ahi[rb];
-            *reinterpret_cast<bf16x8*>(&tlo[t_wr + 16 * rb * kTS]) = alo[rb];
-          }
+          put(0, ap[0][0], ap[1][0]);
+          put(1, ap[0][1], ap[1][1]);
           wave_lds_sync();
         }
         if constexpr (DOT) {
@@ -349,36 +369,49 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
           for (int nb = 0; nb < MB; ++nb) {
             if (nb >= n_mb) continue;
 #pragma unroll
-            for (int rb = 0; rb < 2; ++rb) {
-              ad[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[rb], fhi[s][nb], ad[rb][nb], 0, 0, 0);
-              ad[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo[rb], fhi[s][nb], ad[rb][nb], 0, 0, 0);
-              if (DT == QR_F32)  // bf16 features and e4m3 codes are exact in their high part
-                ad[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[rb], flo[s][nb], ad[rb][nb], 0, 0, 0);
-            }
+            for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+              for (int k = 0; k < PF; ++k)
+#pragma unroll
+                for (int i = 0; i + k < P; ++i)
+                  ad[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[rb][i], fp[s][nb][k], ad[rb][nb], 0, 0, 0);
           }
         }
         if constexpr (DF) {
 #pragma unroll
           for (int cb = 0; cb < 2; ++cb) {
-            const bf16x4 h0 = lds_read_tr(&thi[t_rd + 16 * cb]);
-            const bf16x4 h1 = lds_read_tr(&thi[t_rd + 16 * cb + 4 * kTS]);
-            const bf16x4 l0 = lds_read_tr(&tlo[t_rd + 16 * cb]);
-            const bf16x4 l1 = lds_read_tr(&tlo[t_rd + 16 * cb + 4 * kTS]);
-            const bf16x8 bhi = __builtin_shufflevector(h0, h1, 0, 1, 2, 3, 4, 5, 6, 7);
-            const bf16x8 blo = __builtin_shufflevector(l0, l1, 0, 1, 2, 3, 4, 5, 6, 7);
+            const bf16x8 g0 = get(0, cb), g1 = get(1, cb);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
               if (mb >= n_mb) continue;
-              mfma3(af[s][cb][mb], whi[mb], wlo[mb], bhi, blo);
+              floatx4& a = af[s][cb][mb];
+#pragma unroll
+              for (int i = 0; i < P; ++i) a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[mb][i], g0, a, 0, 0, 0);
+#pragma unroll
+              for (int i = 0; i + 1 < P; ++i) a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[mb][i], g1, a, 0, 0, 0);
             }
           }
           wave_lds_sync();
+          if constexpr (P == 3) {  // the third part, where the first was
+            put(0, ap[0][2], ap[1][2]);
+            wave_lds_sync();
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+              const bf16x8 g2 = get(0, cb);
+#pragma unroll
+              for (int mb = 0; mb < MB; ++mb) {
+                if (mb < n_mb)
+                  af[s][cb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[mb][0], g2, af[s][cb][mb], 0, 0, 0);
+              }
+            }
+            wave_lds_sync();
+          }
         }
       }
       if constexpr (DOT) {
         // lane holds D[4 kb + i][row] of each (pixel row, slot block): four
         // pixels of a slot
-        float* const d = reinterpret_cast<float*>(thi);
+        float* const d = reinterpret_cast<float*>(tile0);
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
@@ -389,28 +422,41 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
       }
     }
     if constexpr (DOT) {
-      __syncthreads();  // every wave has left its sums (and built its weights of these pixels)
-      // the waves whose tiles hold sums of these pixels: column groups of pixel
-      // group pb % pgroups that have columns
-      const int w0 = (pb % pgroups) * cgroups, nw = min(cgroups, (n_sc + MS - 1) / MS);
-      const int q = threadIdx.x & (kPB - 1), p = pb * kPB + q;
-      const float* const d = reinterpret_cast<const float*>(B.stage + w0 * BwdLds<NW>::kTileBytes) + q;
-      uint32_t m = B.smask[p];
-      const int first = threadIdx.x / kPB;
-      for (int k = 0; k < first; ++k) m &= m - 1u;
-      for (int j = B.sj[p] + first; m; j += 2 * NW) {
-        const int sl = __builtin_ctz(m);
-        float x = 0.f;
-        for (int w = 0; w < nw; ++w) x += d[w * (BwdLds<NW>::kTileBytes / sizeof(float)) + sl * kDotStride];
-        if (DT == QR_FP8_E4M3) x *= B.sscale[base + sl];
-        s_w[j] = add ? s_w[j] + x : x;
-        for (int k = 0; k < 2 * NW; ++k) m &= m - 1u;
+      // the dots of pixel p's slots, every `step`-th from the first-th on: the
+      // sum over nw tiles
+      const auto take = [&](int p, int first, int step, const float* d, int nw) {
+        uint32_t m = B.smask[p];
+        for (int k = 0; k < first; ++k) m &= m - 1u;
+        for (int j = B.sj[p] + first; m; j += step) {
+          const int sl = __builtin_ctz(m);
+          float x = 0.f;
+          for (int w = 0; w < nw; ++w) x += d[w * (BwdLds<NW>::kTileBytes / sizeof(float)) + sl * kDotStride];
+          if (DT == QR_FP8_E4M3) x *= B.sscale[base + sl];
+          s_w[j] = add ? s_w[j] + x : x;
+          for (int k = 0; k < step; ++k) m &= m - 1u;
+        }
+      };
+      if (cgroups == 1) {  // a wave has all columns of its pixels, and alone reads their weights
+        if (mine) {
+          wave_lds_sync();
+          const int q = lane & (kPB - 1);
+          take(pb * kPB + q, lane / kPB, 2, reinterpret_cast<const float*>(tile0) + q, 1);
+          wave_lds_sync();
+        }
+      } else {
+        __syncthreads();  // every wave has left its sums (and built its weights of these pixels)
+        // the waves whose tiles hold sums of these pixels: column groups of pixel
+        // group pb % pgroups that have columns
+        const int w0 = (pb % pgroups) * cgroups, nw = min(cgroups, (n_sc + MS - 1) / MS);
+        const int q = threadIdx.x & (kPB - 1);
+        take(pb * kPB + q, threadIdx.x / kPB, 2 * NW,
+             reinterpret_cast<const float*>(B.stage + w0 * BwdLds<NW>::kTileBytes) + q, nw);
+        __syncthreads();  // the tiles are free again
       }
-      __syncthreads();  // the tiles are free again
     }
   }
 
-  if constexpr (DF) {
+  if (DF && gg.grad_features) {
     // lane holds dF[4 kb + i][row] of each (slot block, column block)
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
@@ -512,7 +558,7 @@ constexpr size_t bwd_dynamic_lds(int K) {
 // without one), and once the feature gradients that read a weight are
 // formed, the dot d_j takes its place. The sweep recomputes each weight and
 // T^Q_j from the records with the walk's own float operations.
-template <int DT, int NW>
+template <int DT, int NW, bool WIDE>
 __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGrad& gg, int tile,
                                                        int K, int dim, const qr_params& prm,
                                                        BwdLds<NW>& B, float* __restrict__ dyn) {
@@ -538,8 +584,10 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
   const Shares<NW> sh(v, gg, 0, tx, ty, wave, lane, dim);
   f32x4 raw[Shares<NW>::kBuf][4];
   sh.prime(raw);
-  const PixelSel sel = quantile_walk<QR_SELECT_QUANTILE>(v, lo, hi, K, pxc, pyc, inside, prm, WL, s_pos, s_w, KP);
+  ListSink sink{s_pos + tid * KP, s_w + tid * KP};
+  const PixelSel sel = quantile_walk<QR_SELECT_QUANTILE>(v, lo, hi, K, pxc, pyc, inside, prm, WL, sink);
   const int ns = sel.ns;
+  if (walker) B.inv[tid] = sel.inv;
   int* const my_pos = s_pos + tid * KP;
   const bool geo = gg.grad_means2d || gg.grad_co;
   // the slots' records, for the sweep: fetched with the slots where LDS is
@@ -602,7 +650,8 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
       if (!early) continue;
       if (k >= 0) {
         rec_mean[s] = WL.mean[k];
-        rec_co[s] = WL.co[k];
+        const float4 c = WL.co[k];  // staged with the conic's 2 b
+        rec_co[s] = make_float4(c.x, 0.5f * c.y, c.z, c.w);
       } else {
         load_record(s, g);
       }
@@ -618,32 +667,37 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
     if (s < kMaxSlots) nslotted = j + 1;
   }
 
-  // ---- feature gradients and dots, 32 slots at a time ----
-  const bool df = gg.grad_features != nullptr;
-  const int rounds = (dim + 511) / 512;
+  // ---- feature gradients and dots, a pass for 32 slots at a time ----
+  // (widths up to 512: both products at once, whether or not both are asked
+  // for; wider: in rounds of 512 columns, the feature gradients of all rounds
+  // before the dots, which replace the weights)
   int j_next = 0;
-  for (int base = 0; base < nslots; base += kSlots) {
+  const auto masks = [&](int base, int n) {
     if (walker) {
       uint32_t m = 0u;
       B.sj[tid] = tid * KP + j_next;
       for (; j_next < nslotted; ++j_next) {
         const int s = my_pos[j_next] - base;
-        if (s >= kSlots) break;
+        if (s >= n) break;
         m |= 1u << s;
       }
       B.smask[tid] = m;
     }
     __syncthreads();
-    const int n = min(kSlots, nslots - base);
-    if (df && geo && rounds == 1) {
-      if (base > 0) sh.prime(raw);
-      stream_slots<DT, NW, true, true>(v, gg, B, s_w, base, n, false, sh, raw, wave, lane, dim);
+  };
+  const auto pass = [&](int base, int n, auto far) {
+    constexpr bool FAR = decltype(far)::value;
+    masks(base, n);
+    if constexpr (!WIDE) {
+      if (FAR) sh.prime(raw);
+      stream_slots<DT, NW, true, true, FAR>(v, gg, B, s_w, base, n, false, sh, raw, wave, lane, dim);
     } else {
-      if (df) {
+      const int rounds = (dim + 511) / 512;
+      if (gg.grad_features) {
         for (int r = 0; r < rounds; ++r) {
           const Shares<NW> shr(v, gg, r, tx, ty, wave, lane, dim);
           shr.prime(raw);
-          stream_slots<DT, NW, true, false>(v, gg, B, s_w, base, n, false, shr, raw, wave, lane, dim);
+          stream_slots<DT, NW, true, false, FAR>(v, gg, B, s_w, base, n, false, shr, raw, wave, lane, dim);
         }
       }
       if (geo) {
@@ -651,12 +705,16 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
         for (int r = 0; r < rounds; ++r) {
           const Shares<NW> shr(v, gg, r, tx, ty, wave, lane, dim);
           shr.prime(raw);
-          stream_slots<DT, NW, false, true>(v, gg, B, s_w, base, n, r > 0, shr, raw, wave, lane, dim);
+          stream_slots<DT, NW, false, true, FAR>(v, gg, B, s_w, base, n, r > 0, shr, raw, wave, lane, dim);
         }
       }
     }
     __syncthreads();  // the masks may be rewritten
-  }
+  };
+  if (nslots > 0) pass(0, min(kSlots, nslots), std::false_type{});
+#pragma unroll 1
+  for (int base = kSlots; base < nslots; base += pass_slots<true>())
+    pass(base, min(pass_slots<true>(), nslots - base), std::true_type{});
   if (walker) slotless<DT>(v, gg, B.inv, s_pos, s_w, tx, ty, wave, lane, dim, nslotted, ns, KP, geo);
   if (!geo) return;
 
@@ -752,8 +810,8 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
     }
   }
   wave_lds_sync();
-  // Every gradient of a slot follows from the moments of its dL/dpower over
-  // the tile's pixels, sum_p dpow_p {1, dx, dy, dx^2, dx dy, dy^2}. A lane takes
+  // The gradients of a slot are sums of its dL/dpower over the tile's pixels,
+  // sum_p dpow_p {dx^2, dx dy, dy^2, 1, a dx + b dy, b dx + c dy}. A lane takes
   // one slot and half a tile row at a time (dy is then one value), so the
   // sums stay in registers; the lanes of a slot are added up by exchanges and
   // the four waves in LDS. (Evaluating the values per slot for all 64 pixels
@@ -779,13 +837,14 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
     for (int mb = 0; mb < n_mb; ++mb) {
       const int sl = mb * 16 + row;
       const float2 mean = rec_mean[min(32 * w + sl, nslots - 1)];
+      const float4 co = rec_co[min(32 * w + sl, nslots - 1)];
       float q[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int h = 0; h < 2; ++h) {  // 32 pixels: two tile rows
         const int p0 = wave * 64 + 32 * h + 8 * kb;
         const float dy = (ty * kTile + p0 / kTile + 0.5f) - mean.y;
         const float dx0 = (tx * kTile + (p0 & 8) + 0.5f);
-        float s0 = 0.f, sx = 0.f, sxx = 0.f;
+        float s0 = 0.f, sx = 0.f, sxx = 0.f, su = 0.f, sv = 0.f;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
           const uint32_t mp = B.smask[p0 + t];
@@ -796,14 +855,15 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
           s0 += d;
           sx += v;
           sxx = fmaf(v, dx, sxx);
+          su = fmaf(d, co.x * dx + co.y * dy, su);
+          sv = fmaf(d, co.y * dx + co.z * dy, sv);
         }
-        const float sy = s0 * dy;
-        q[0] += s0;
-        q[1] += sx;
-        q[2] += sy;
-        q[3] += sxx;
-        q[4] = fmaf(sx, dy, q[4]);
-        q[5] = fmaf(sy, dy, q[5]);
+        q[0] += sxx;
+        q[1] = fmaf(sx, dy, q[1]);
+        q[2] = fmaf(s0 * dy, dy, q[2]);
+        q[3] += s0;
+        q[4] += su;
+        q[5] += sv;
       }
       // over the slot's four lanes, 16 apart
 #pragma unroll
@@ -820,19 +880,11 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
     const int ls = conic ? tid >> 2 : (tid - 4 * kSlots) >> 1, k = conic ? tid & 3 : 4 + (tid & 1);
     const int sl = 32 * w + ls;
     if (tid < 6 * kSlots && sl < nslots) {
-      float q[6];
-#pragma unroll
-      for (int i = 0; i < 6; ++i)
-        q[i] = mom[ls * 8 + i] + mom[(kSlots + ls) * 8 + i] + mom[(2 * kSlots + ls) * 8 + i] +
-               mom[(3 * kSlots + ls) * 8 + i];
-      const float4 co = rec_co[sl];
+      const int at = ls * 8 + k;
+      const float sum = mom[at] + mom[kSlots * 8 + at] + mom[2 * kSlots * 8 + at] + mom[3 * kSlots * 8 + at];
       const int64_t g = B.sgid[sl];
-      const float val = k == 0   ? -0.5f * q[3]
-                        : k == 1 ? -q[4]
-                        : k == 2 ? -0.5f * q[5]
-                        : k == 3 ? q[0] / co.w  // alpha' = o G: dL/do = dL/dpower / o
-                        : k == 4 ? co.x * q[1] + co.y * q[2]
-                                 : co.y * q[1] + co.z * q[2];
+      // (alpha' = o G: dL/do = dL/dpower / o)
+      const float val = k >= 4 ? sum : k == 1 ? -sum : k == 3 ? sum / rec_co[sl].w : -0.5f * sum;
       if (conic && gg.grad_co) atomic_add(gg.grad_co + 4 * g + k, val);
       if (!conic && gg.grad_means2d) atomic_add(gg.grad_means2d + 2 * g + (k - 4), val);
     }
@@ -843,12 +895,12 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
 // Two waves per SIMD (registers of the MFMA operands and accumulators).
 constexpr int kBwdWavesPerSimd = 2;
 
-template <int DT, int NW>
+template <int DT, int NW, bool WIDE>
 __global__ void __launch_bounds__(64 * NW, kBwdWavesPerSimd)
 quantile_backward_kernel(ViewArgs v, GradPtrs gp, int n_tiles, qr_params prm, int K, int dim) {
   extern __shared__ __attribute__((aligned(16))) float dyn_lds[];
   __shared__ BwdLds<NW> B;
-  quantile_backward_tile<DT, NW>(to_global(v), to_global(gp), xcd_remap(blockIdx.x, n_tiles), K, dim,
+  quantile_backward_tile<DT, NW, WIDE>(to_global(v), to_global(gp), xcd_remap(blockIdx.x, n_tiles), K, dim,
                                  prm, B, dyn_lds);
 }
 
@@ -858,7 +910,7 @@ __device__ __forceinline__ GradPtrs grad_ptrs(const qr_view_grad& g) {
 
 // Many views in one launch, one workgroup per (view, tile) item, items dealt
 // to the XCDs in contiguous runs of the schedule.
-template <int DT, int NW>
+template <int DT, int NW, bool WIDE>
 __global__ void __launch_bounds__(64 * NW, kBwdWavesPerSimd)
 quantile_backward_batched_grid_kernel(const qr_view* __restrict__ views,
                                       const qr_view_grad* __restrict__ grads,
@@ -868,7 +920,7 @@ quantile_backward_batched_grid_kernel(const qr_view* __restrict__ views,
   __shared__ BwdLds<NW> B;
   const uint32_t packed = __builtin_amdgcn_readfirstlane(schedule[xcd_remap(blockIdx.x, n_items)]);
   const uint32_t vi = packed >> kViewShift;
-  quantile_backward_tile<DT, NW>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
+  quantile_backward_tile<DT, NW, WIDE>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
                                  static_cast<int>(packed & kTileMask), K, dim, prm, B, dyn_lds);
 }
 
@@ -880,7 +932,7 @@ __device__ __forceinline__ uint32_t bwd_queue_begin(int64_t n_items, int q) {
   return static_cast<uint32_t>(n_items * q / kBwdXcdQueues);
 }
 
-template <int DT, int NW>
+template <int DT, int NW, bool WIDE>
 __global__ void __launch_bounds__(64 * NW, kBwdWavesPerSimd)
 quantile_backward_batched_kernel(const qr_view* __restrict__ views,
                                  const qr_view_grad* __restrict__ grads,
@@ -912,7 +964,7 @@ quantile_backward_batched_kernel(const qr_view* __restrict__ views,
     if (item >= n_items) break;
     const uint32_t packed = __builtin_amdgcn_readfirstlane(schedule[item]);
     const uint32_t vi = packed >> kViewShift;
-    quantile_backward_tile<DT, NW>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
+    quantile_backward_tile<DT, NW, WIDE>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
                                    static_cast<int>(packed & kTileMask), K, dim, prm, B, dyn_lds);
   }
 }
@@ -934,16 +986,19 @@ static_assert(sizeof(BwdLds<4>) + 64 + bwd_dynamic_lds(QR_MAX_K) <= kCuLds, "the
 
 using namespace qr;
 
-#define QR_BWD_DISPATCH_NW(dt, NW)                    \
+// QR_LAUNCH(feature type, waves, columns in rounds) for the runtime values.
+#define QR_BWD_DISPATCH_NW(dt, NW, WIDE)              \
   switch (dt) {                                       \
-    case QR_F32: QR_LAUNCH(QR_F32, NW); break;        \
-    case QR_BF16: QR_LAUNCH(QR_BF16, NW); break;      \
-    default: QR_LAUNCH(QR_FP8_E4M3, NW); break;       \
+    case QR_F32: QR_LAUNCH(QR_F32, NW, WIDE); break;  \
+    case QR_BF16: QR_LAUNCH(QR_BF16, NW, WIDE); break; \
+    default: QR_LAUNCH(QR_FP8_E4M3, NW, WIDE); break; \
   }
-#define QR_BWD_DISPATCH(dt, wide)                     \
+#define QR_BWD_DISPATCH(dt, eight, dim)               \
   do {                                                \
-    if (wide) { QR_BWD_DISPATCH_NW(dt, 8) }           \
-    else { QR_BWD_DISPATCH_NW(dt, 4) }                \
+    if ((eight) && (dim) <= 512) { QR_BWD_DISPATCH_NW(dt, 8, false) } \
+    else if (eight) { QR_BWD_DISPATCH_NW(dt, 8, true) } \
+    else if ((dim) <= 512) { QR_BWD_DISPATCH_NW(dt, 4, false) } \
+    else { QR_BWD_DISPATCH_NW(dt, 4, true) }          \
   } while (0)
 
 extern "C" int qr_render_quantile_backward(void* stream, int32_t width, int32_t height,
@@ -970,12 +1025,12 @@ extern "C" int qr_render_quantile_backward(void* stream, int32_t width, int32_t 
                    reinterpret_cast<const float4*>(conic_opacity), features, feature_scale,
                    nullptr, nullptr, nullptr};
   const GradPtrs gp{grad_out, grad_features, grad_means2d, grad_conic_opacity};
-  const bool wide = K > kBwdPairK && K <= kBwdWideK;
+  const bool eight = K > kBwdPairK && K <= kBwdWideK;
   const size_t lds = bwd_dynamic_lds(K);
-#define QR_LAUNCH(DT, NW)                                                                              \
-  hipLaunchKernelGGL((quantile_backward_kernel<DT, NW>), dim3(n_tiles), dim3(64 * NW), lds, s, v, gp, \
+#define QR_LAUNCH(DT, NW, WIDE)                                                                              \
+  hipLaunchKernelGGL((quantile_backward_kernel<DT, NW, WIDE>), dim3(n_tiles), dim3(64 * NW), lds, s, v, gp, \
                      n_tiles, *prm, K, dim)
-  QR_BWD_DISPATCH(dtype, wide);
+  QR_BWD_DISPATCH(dtype, eight, dim);
 #undef QR_LAUNCH
   return check_launch("qr_render_quantile_backward");
 }
@@ -1007,23 +1062,23 @@ extern "C" int qr_render_quantile_batched_backward(void* stream, int32_t n_views
     return fail(QR_ERR_UNSUPPORTED, "%s: the quantile selection only", name);
   if (n_items == 0) return QR_OK;
   hipStream_t s = as_stream(stream);
-  const bool wide = K > kBwdPairK && K <= kBwdWideK;
+  const bool eight = K > kBwdPairK && K <= kBwdWideK;
   const size_t lds = bwd_dynamic_lds(K);
   if (n_workgroups == 0) {
     const int ni = static_cast<int>(n_items);
-#define QR_LAUNCH(DT, NW)                                                                          \
-  hipLaunchKernelGGL((quantile_backward_batched_grid_kernel<DT, NW>), dim3(ni), dim3(64 * NW), lds, \
+#define QR_LAUNCH(DT, NW, WIDE)                                                                          \
+  hipLaunchKernelGGL((quantile_backward_batched_grid_kernel<DT, NW, WIDE>), dim3(ni), dim3(64 * NW), lds, \
                      s, views, grads, schedule, ni, *prm, K, dim)
-    QR_BWD_DISPATCH(dtype, wide);
+    QR_BWD_DISPATCH(dtype, eight, dim);
 #undef QR_LAUNCH
     return check_launch(name);
   }
   auto* counter = static_cast<uint32_t*>(workspace);
   hipLaunchKernelGGL(reset_bwd_counter_kernel, dim3(1), dim3(64), 0, s, counter);
-#define QR_LAUNCH(DT, NW)                                                                           \
-  hipLaunchKernelGGL((quantile_backward_batched_kernel<DT, NW>), dim3(n_workgroups), dim3(64 * NW), \
+#define QR_LAUNCH(DT, NW, WIDE)                                                                           \
+  hipLaunchKernelGGL((quantile_backward_batched_kernel<DT, NW, WIDE>), dim3(n_workgroups), dim3(64 * NW), \
                      lds, s, views, grads, schedule, n_items, counter, *prm, K, dim)
-  QR_BWD_DISPATCH(dtype, wide);
+  QR_BWD_DISPATCH(dtype, eight, dim);
 #undef QR_LAUNCH
   return check_launch(name);
 }

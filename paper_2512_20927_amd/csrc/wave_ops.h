@@ -94,6 +94,26 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8& hi, bf16x8& 
   lo = __builtin_bit_cast(bf16x8, l);
 }
 
+// x as P bfloat16 parts, each the rounding of what the parts before it leave
+// (P = 2: split8; P = 3 holds float32's 24 bits).
+template <int P>
+__device__ __forceinline__ void split_parts(const float (&x)[8], bf16x8 (&part)[P]) {
+  if constexpr (P == 1) {
+    bf16x8 rest;
+    split8(x, part[0], rest);
+  } else {
+    split8(x, part[0], part[1]);
+    if constexpr (P == 3) {
+      float r[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        r[i] = (x[i] - static_cast<float>(part[0][i])) - static_cast<float>(part[1][i]);
+      bf16x8 rest;
+      split8(r, part[2], rest);
+    }
+  }
+}
+
 // acc += A B for split operands: hi.hi + lo.hi + hi.lo (the lo.lo term is
 // below 2^-16 of the product).
 __device__ __forceinline__ void mfma3(floatx4& acc, const bf16x8& ahi, const bf16x8& alo,
