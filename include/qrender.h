@@ -235,9 +235,9 @@ int qr_bin_sort_workspace_size(int64_t n, int32_t tiles_x, int32_t tiles_y,
  * Emits one pair per tile in each tile_rect, keyed (tile id << 32) | bits of
  * the float32 depth: a bucket sort by tile (count, exclusive scan, scatter
  * into each tile's range) followed by an independent sort of each tile's
- * bucket by (depth bits << 32 | Gaussian index) - a bitonic sort in LDS for
- * buckets of up to 2,048 keys, a single-workgroup LSD radix sort through the
- * workspace for longer ones. The keys are unique, so each tile's list is
+ * bucket by (depth bits << 32 | Gaussian index) - a bitonic sort in registers
+ * for buckets of up to 2,048 keys, a single-workgroup LSD radix sort through
+ * the workspace for longer ones. The keys are unique, so each tile's list is
  * ordered by (depth, index) whatever order the scatter produced.
  * Inputs: tile_rect, tiles_touched, depth as written by qr_project.
  * Outputs: sorted_gid u32[capacity] (Gaussian index of each sorted pair);
