@@ -40,6 +40,7 @@ KERNEL_SOURCES = {
                         "paper_2512_20927_amd/csrc/common.h"],
     "render_dense": ["paper_2512_20927_amd/csrc/render_dense.hip",
                      "paper_2512_20927_amd/csrc/dense_walk.h",
+                     "paper_2512_20927_amd/csrc/wave_ops.h",
                      "paper_2512_20927_amd/csrc/quantile_select.h",
                      "paper_2512_20927_amd/csrc/render_common.h",
                      "paper_2512_20927_amd/csrc/common.h"],
