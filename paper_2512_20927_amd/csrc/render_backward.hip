@@ -398,21 +398,35 @@ dense_backward_geo_kernel(int W, int H, int tiles_x, int n_units, qr_params prm,
     for (int p = 0; p < 4; ++p) {
       tp[p] = 0.f;
       const int gx = tx * kTile + ci, gy = ty * kTile + strip * 4 + p;
+      // all of a pixel's loads are in flight together: none under a
+      // condition, pixels and columns past the edges read a valid address
+      // and are zeroed (the kernel, 500k Gaussians at 640x480: 496 us with
+      // each step's loads under its bounds check, 480 without)
+      const bool in = gx < W && gy < H;
+      const int64_t row = (static_cast<int64_t>(min(gy, H - 1)) * W + min(gx, W - 1)) * dim;
+      f32x4 g[4][2], o[4][2];
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         const int c = kGeoCols * wave + 32 * s + 8 * kb;
-        float g8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (gx < W && gy < H && c < dim) {
-          const int64_t base = (static_cast<int64_t>(gy) * W + gx) * dim + c;
-          const f32x4 a = *reinterpret_cast<const QR_GLOBAL f32x4*>(grad_out + base);
-          const f32x4 b = *reinterpret_cast<const QR_GLOBAL f32x4*>(grad_out + base + 4);
-          const f32x4 oa = *reinterpret_cast<const QR_GLOBAL f32x4*>(out + base);
-          const f32x4 ob = *reinterpret_cast<const QR_GLOBAL f32x4*>(out + base + 4);
-          g8[0] = a.x; g8[1] = a.y; g8[2] = a.z; g8[3] = a.w;
-          g8[4] = b.x; g8[5] = b.y; g8[6] = b.z; g8[7] = b.w;
-          tp[p] += a.x * oa.x + a.y * oa.y + a.z * oa.z + a.w * oa.w + b.x * ob.x + b.y * ob.y +
-                   b.z * ob.z + b.w * ob.w;
+        const int64_t base = row + (c < dim ? c : 0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          g[s][q] = *reinterpret_cast<const QR_GLOBAL f32x4*>(grad_out + base + 4 * q);
+          o[s][q] = *reinterpret_cast<const QR_GLOBAL f32x4*>(out + base + 4 * q);
         }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const bool live = in && kGeoCols * wave + 32 * s + 8 * kb < dim;
+        float g8[8];
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float x = g[s][i >> 2][i & 3];
+          t = i == 0 ? x * o[s][0][0] : t + x * o[s][i >> 2][i & 3];
+          g8[i] = live ? x : 0.f;
+        }
+        tp[p] += live ? t : 0.f;
         split8(g8, ghi[p][s], glo[p][s]);
       }
     }
@@ -453,8 +467,7 @@ dense_backward_geo_kernel(int W, int H, int tiles_x, int n_units, qr_params prm,
       L.co[par][tid] = make_float4(rco.x, rco.y, rco.z, rco.w);
     }
     if (__syncthreads_count(!done) == 0) break;  // publishes the records; uniform
-    const bool prefetch = tid < kWalkBatch && nb + tid < hi;
-    if (prefetch) rgid = static_cast<int>(sorted_gid[nb + tid]);
+    rgid = static_cast<int>(sorted_gid[min(nb + (lane & (kWalkBatch - 1)), hi - 1)]);
 
     // partial dots over this wave's columns: D[pixel][entry], A = G, B = F^T
     // (entry 16 e + ci, columns 128 w + 32 s + 8 kb .. + 7; columns past dim
@@ -515,10 +528,8 @@ dense_backward_geo_kernel(int W, int H, int tiles_x, int n_units, qr_params prm,
     float al[kWalkQ];
     L.part[wave][lane] =
         walk_alpha8(L.mean[par], L.co[par], kWalkQ * wave, cnt, done, pxc, pyc, prm, al);
-    if (prefetch) {
-      rmean = means2d[rgid];
-      rco = conic_opacity[rgid];
-    }
+    rmean = means2d[rgid];
+    rco = conic_opacity[rgid];
 
 
     __syncthreads();
@@ -650,15 +661,28 @@ dense_backward_feat_kernel(int W, int H, int tiles_x, int n_units, int n_slices,
   const bool wcols = slice * kFeatCols + 16 * wave < dim;  // uniform
   bf16x8 bhi[8], blo[8];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    float x[8];
+  for (int k0 = 0; k0 < 8; k0 += 4) {
+    // 32 loads in flight: none under a condition, pixels and columns past the
+    // edges read a valid address and are zeroed
+    float x[4][8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int p = 32 * k + 8 * kb + t;
-      const int gx = tx * kTile + (p % kTile), gy = ty * kTile + (p / kTile);
-      x[t] = (wcols && gx < W && gy < H) ? grad_out[(static_cast<int64_t>(gy) * W + gx) * dim + col] : 0.f;
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int p = 32 * (k0 + k) + 8 * kb + t;
+        const int gx = min(tx * kTile + (p % kTile), W - 1), gy = min(ty * kTile + (p / kTile), H - 1);
+        x[k][t] = grad_out[(static_cast<int64_t>(gy) * W + gx) * dim + (wcols ? col : 0)];
+      }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int p = 32 * (k0 + k) + 8 * kb + t;
+        const int gx = tx * kTile + (p % kTile), gy = ty * kTile + (p / kTile);
+        x[k][t] = wcols && gx < W && gy < H ? x[k][t] : 0.f;
+      }
+      split8(x[k], bhi[k0 + k], blo[k0 + k]);
     }
-    split8(x, bhi[k], blo[k]);
   }
 
   int rgid = -1;
@@ -683,8 +707,7 @@ dense_backward_feat_kernel(int W, int H, int tiles_x, int n_units, int n_slices,
     // publishes the records (and orders this batch's weight stores after the
     // previous batch's MFMA reads); uniform exit once every pixel stopped
     if (__syncthreads_count(!done) == 0) break;
-    const bool prefetch = tid < kWalkBatch && nb + tid < hi;
-    if (prefetch) rgid = static_cast<int>(sorted_gid[nb + tid]);
+    rgid = static_cast<int>(sorted_gid[min(nb + (lane & (kWalkBatch - 1)), hi - 1)]);
     // Eq. 1 along this pixel's ray, in list order, as two halves of the
     // batch: both take alpha' of their entries at once; the first half then
     // runs the transmittance chain with the stop test, and the second
@@ -702,6 +725,7 @@ dense_backward_feat_kernel(int W, int H, int tiles_x, int n_units, int n_slices,
       }
     }
     const auto chain = [&]() {
+      float w8[kHalf / 8][8];
 #pragma unroll
       for (int j = 0; j < kHalf; ++j) {
         float w = 0.f;
@@ -714,10 +738,18 @@ dense_backward_feat_kernel(int W, int H, int tiles_x, int n_units, int n_slices,
             T = T_test;
           }
         }
-        const int e = kHalf * half + j;
-        const __bf16 h = static_cast<__bf16>(w);
-        L.whi[e * kWT + pix] = h;
-        L.wlo[e * kWT + pix] = static_cast<__bf16>(w - static_cast<float>(h));
+        w8[j >> 3][j & 7] = w;
+      }
+#pragma unroll
+      for (int q = 0; q < kHalf / 8; ++q) {
+        bf16x8 h, l;
+        split8(w8[q], h, l);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int e = kHalf * half + 8 * q + j;
+          L.whi[e * kWT + pix] = h[j];
+          L.wlo[e * kWT + pix] = l[j];
+        }
       }
     };
     if (half == 0) {
@@ -733,10 +765,8 @@ dense_backward_feat_kernel(int W, int H, int tiles_x, int n_units, int n_slices,
       L.Tf[pix] = T;
       L.df[pix] = done;
     }
-    if (prefetch) {
-      rmean = means2d[rgid];
-      rco = conic_opacity[rgid];
-    }
+    rmean = means2d[rgid];
+    rco = conic_opacity[rgid];
     __syncthreads();
     if (half == 0) {
       T = L.Tf[pix];
