@@ -60,11 +60,10 @@ static_assert(kDB == kWalkBatch && kDQ == kWalkQ, "the strip's batches are the s
 struct DenseLds {
   __attribute__((aligned(16))) __bf16 whi[kStripPix * kWS];
   __attribute__((aligned(16))) __bf16 wlo[kStripPix * kWS];
-  float2 mean[kDB];
-  float4 co[kDB];
-  // ids of the batch, double-buffered by batch parity: the second column
-  // group's loads read them after the last barrier of the batch, while wave
-  // 0 may already be staging the next batch
+  // records and ids, double-buffered by batch parity: the next batch's are
+  // staged between the two barriers of the current one
+  float2 mean[2][kDB];
+  float4 co[2][kDB];
   __attribute__((aligned(16))) uint32_t gid[2][kDB];
   float part[4][kStripPix];   // product of (1 - alpha') over a wave's eight entries
   float tend[4][kStripPix];   // T after a wave's eight entries (before its stop)
@@ -248,10 +247,7 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
   const int lo = static_cast<int>(v.tile_offsets[tile]);
   const int hi = static_cast<int>(v.tile_offsets[tile + 1]);
   const int coff = 16 * (ci & 3) + 4 * (ci >> 2);  // the lane's columns in a group
-  int par = 0;  // parity of the batches staged so far (selects the id buffer)
-  // The next batch's ids and records are requested by threads 0..31 while
-  // the current batch is contracted, and staged into LDS at the top of the
-  // next iteration.
+  int par = 0;  // parity of the batches staged so far (selects the record buffer)
   for (int c0 = 0; c0 < dim; c0 += kPassCols) {
     // this wave's column groups in the pass: base column and width (0: none)
     int gbase[kStripGroups], gw[kStripGroups];
@@ -278,24 +274,42 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
       rmean = v.means2d[rgid];
       rco = v.conic_opacity[rgid];
     }
+    // Records are staged one batch ahead, between the two barriers of a
+    // batch, requested two ahead and their ids three (staged at the top of
+    // their own batch, which took a third barrier: 16 float32 frames of
+    // 640x480 4.36 ms, now 4.25; bfloat16 3.64 and 3.57).
+    // Every id slot holds a valid row: slots past the list repeat its last
+    // entry (their weights are zero). Only wave 0's first 32 lanes' values
+    // are staged; the loads are unconditional, so that they stay in flight.
+    const auto id_at = [&](int b) {
+      return static_cast<int>(v.sorted_gid[min(b + (lane & (kDB - 1)), hi - 1)]);
+    };
+    const auto stage = [&](int p, int cnt) {
+      const int g0 = __shfl(rgid, 0);
+      if (tid < kDB) {
+        L.gid[p][tid] = static_cast<uint32_t>(tid < cnt ? rgid : g0);
+        L.mean[p][tid] = make_float2(rmean.x, rmean.y);
+        L.co[p][tid] = make_float4(rco.x, rco.y, rco.z, rco.w);
+      }
+    };
+    int rgid2 = 0;
+    if (first) {  // uniform
+      // the previous pass may still read its records: both buffers are free
+      // only after its last batch's MFMAs
+      if (c0 != 0) __syncthreads();
+      stage(par, hi - lo);
+      rgid = id_at(lo + kDB);
+      rgid2 = id_at(lo + 2 * kDB);
+      __syncthreads();
+    }
     for (int batch = lo; batch < hi; batch += kDB) {
       if (__ballot(!done) == 0ull) break;
       const int cnt = min(kDB, hi - batch);
       const int nb = batch + kDB;
-      // records of the batch (the previous batch's were last read before the
-      // second barrier of its iteration, which every wave has passed; its ids
-      // are in the other buffer)
-      uint32_t* const gid = L.gid[par];
+      const uint32_t* const gid = L.gid[par];
+      const float2* const mean = L.mean[par];
+      const float4* const co = L.co[par];
       par ^= 1;
-      // every id slot holds a valid row: slots past the list repeat the
-      // batch's first id (their weights are zero)
-      const int g0 = __shfl(rgid, 0);
-      if (tid < kDB) gid[tid] = static_cast<uint32_t>(tid < cnt ? rgid : g0);
-      if (tid < cnt) {
-        L.mean[tid] = make_float2(rmean.x, rmean.y);
-        L.co[tid] = make_float4(rco.x, rco.y, rco.z, rco.w);
-      }
-      __syncthreads();
 
       // feature rows of the batch for this wave's first group, requested now
       // so that the loads overlap the walk (the second group's are requested
@@ -314,12 +328,16 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
 #pragma unroll
         for (int t = 0; t < 8; ++t) raw[t] = load_raw4<DT>(v, g8[t], dim, col);
       };
+      if (batch == lo) {  // uniform: the later ones are requested a batch ahead
+        rmean = v.means2d[rgid];
+        rco = v.conic_opacity[rgid];
+      }
       load_group(0);
 
       // walk (the split walk of dense_walk.h): alpha' of this wave's eight
       // entries and the product of their (1 - alpha')
       float al[kDQ];
-      L.part[wave][lane] = walk_alpha8(L.mean, L.co, kDQ * wave, cnt, done, pxc, pyc, prm, al);
+      L.part[wave][lane] = walk_alpha8(mean, co, kDQ * wave, cnt, done, pxc, pyc, prm, al);
       __syncthreads();
 
       // T at the start of the eight entries, their weights in list order
@@ -342,26 +360,25 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
       L.info[wave][lane] = inf;
       const unsigned long long b = __ballot(any);
       if (lane == 0) L.busy[wave] = b;
+      // the next batch's records (their buffer's last reads, the previous
+      // batch's MFMA phase, lie before this batch's first barrier); then the
+      // records of the batch after it and the ids of the third are requested
+      stage(par, hi - nb);
+      rgid = rgid2;
+      rmean = v.means2d[rgid];
+      rco = v.conic_opacity[rgid];
+      rgid2 = id_at(nb + 2 * kDB);
       __syncthreads();
 
       // the pixel's state after the batch (the same in every wave)
       walk_fold(&L.tend[0][0], &L.info[0][0], kStripPix, lane, batch - lo, T, done, ncon);
       const unsigned long long busy = L.busy[0] | L.busy[1] | L.busy[2] | L.busy[3];
-      // the next batch's ids (its records are requested after the first
-      // group's MFMAs, once the ids have arrived)
-      rgid = static_cast<int>(v.sorted_gid[min(nb + (lane & (kDB - 1)), hi - 1)]);
 
       // F^T W^T on the matrix cores, one column group at a time: A = this
       // wave's features (rows permuted within the group), B = the weights of
       // 16 pixels
 #pragma unroll
       for (int k = 0; k < kStripGroups; ++k) {
-        if (k == 1) {
-          // the next batch's records (their ids, requested before the first
-          // group's MFMAs, have arrived)
-          rmean = v.means2d[rgid];
-          rco = v.conic_opacity[rgid];
-        }
         bf16x8 ahi[4], alo[4];
         convert_group<DT>(raw, ahi, alo);
         if (gw[k] != 0) mfma_group<DT>(acc[k], ahi, alo, L.whi, L.wlo, busy, ci, kb);
@@ -382,7 +399,7 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
 }
 
 // Narrow features (dim <= 64: one column group). The strip decomposition
-// above splits each batch's walk over four waves and pays three barriers and a
+// above splits each batch's walk over four waves and pays two barriers and a
 // cross-wave fold per batch for it; with one column group there is little
 // MFMA work to hide that behind. Here one workgroup takes a whole tile: wave w
 // owns strip w (tile rows 4w .. 4w + 3), each lane walks its pixel's chain
