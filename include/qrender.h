@@ -49,8 +49,8 @@ extern "C" {
 #define QR_TILE 16
 /* K (quantile Gaussians per ray) ranges over [1, QR_MAX_K] in every entry
  * point, backward passes included: the paper trains at K = 40 and sweeps K up
- * to 50. A workgroup keeps each pixel's <= K selections in LDS (8 bytes
- * each), so K above about 40 leaves room for one workgroup per CU. */
+ * to 50. The Top-K sampler and the backward keep each pixel's <= K selections
+ * in LDS (8 bytes each), so a large K leaves them fewer workgroups per CU. */
 #define QR_MAX_K 64
 /* Feature width D: a positive multiple of 16 (the column block of the matrix
  * core contractions of the dense blend and the backward passes) up to
