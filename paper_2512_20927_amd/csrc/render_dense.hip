@@ -21,9 +21,8 @@
 //     contracts them with its own column groups of F on
 //     v_mfma_f32_16x16x32_bf16 as out^T = F^T W^T, both operands split into
 //     bfloat16 pairs and the product formed as F_hi W_hi + F_lo W_hi +
-//     F_hi W_lo with float32 accumulation (bfloat16 features and e4m3 codes
-//     are exact in F_hi, so their F_lo term is dropped; an e4m3 row's scale is
-//     multiplied into its weights): float32-class accuracy (below
+//     F_hi W_lo with float32 accumulation (bfloat16 features are exact in
+//     F_hi, so their F_lo term is dropped): float32-class accuracy (below
 //     2^-16 of each product) at the bfloat16 matrix rate;
 //   - the MFMA rows of a 64-column group are permuted (row i of column tile c
 //     is column 16 (i % 4) + 4 (i / 4) + c), so that a lane's operand values
@@ -90,14 +89,15 @@ __device__ __forceinline__ f32x4 load_raw4(const GView& v, uint32_t g, int dim, 
 }
 
 // A operands (bfloat16 pairs) of one column group from its raw rows: column
-// tile c takes component c of the lane's eight rows. (split8 converts two
+// tile c takes component c of the lane's eight rows (e4m3 codes times the
+// rows' scales sc, decoded here so that the loads stay in flight). (split8 converts two
 // values per instruction; a value at a time, and with the next batch's records
 // requested under a condition, which the compiler waits for on the spot, 16
 // float32 frames of 640x480 took 4.58 ms, now 4.43; bfloat16 rows, one frame of
 // 500k Gaussians, 0.278 and 0.266.)
 template <int DT>
-__device__ __forceinline__ void convert_group(const f32x4 (&raw)[8], bf16x8 (&ahi)[4],
-                                              bf16x8 (&alo)[4]) {
+__device__ __forceinline__ void convert_group(const f32x4 (&raw)[8], const float (&sc)[8],
+                                              bf16x8 (&ahi)[4], bf16x8 (&alo)[4]) {
   if constexpr (DT == QR_BF16) {
     // two codes per 32-bit word, column c in word c / 2
 #pragma unroll
@@ -109,24 +109,19 @@ __device__ __forceinline__ void convert_group(const f32x4 (&raw)[8], bf16x8 (&ah
         ahi[c][t] = __builtin_bit_cast(__bf16, code);
       }
   } else if constexpr (DT == QR_FP8_E4M3) {
-    // e4m3 codes are bfloat16 values (3 of 7 mantissa bits); the row's scale
-    // is in the weights
+    // two columns at a time: sixteen decoded values in registers, not 32
 #pragma unroll
-    for (int t = 0; t < 8; t += 2) {
-      f32x2 x[2][2];
+    for (int h = 0; h < 2; ++h) {
+      float x[2][8];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int r = __float_as_int(raw[t + i].x);
-        x[i][0] = __builtin_bit_cast(f32x2, __builtin_amdgcn_cvt_pk_f32_fp8(r, false));
-        x[i][1] = __builtin_bit_cast(f32x2, __builtin_amdgcn_cvt_pk_f32_fp8(r, true));
+      for (int t = 0; t < 8; ++t) {
+        const int r = __float_as_int(raw[t].x);
+        const auto d = h ? __builtin_amdgcn_cvt_pk_f32_fp8(r, true) : __builtin_amdgcn_cvt_pk_f32_fp8(r, false);
+        x[0][t] = d[0] * sc[t];
+        x[1][t] = d[1] * sc[t];
       }
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const uint32_t both = __builtin_amdgcn_perm(__float_as_uint(x[1][c >> 1][c & 1]),
-                                                    __float_as_uint(x[0][c >> 1][c & 1]), 0x07060302);
-        ahi[c][t] = __builtin_bit_cast(__bf16, static_cast<uint16_t>(both & 0xFFFFu));
-        ahi[c][t + 1] = __builtin_bit_cast(__bf16, static_cast<uint16_t>(both >> 16));
-      }
+      split8(x[0], ahi[2 * h], alo[2 * h]);
+      split8(x[1], ahi[2 * h + 1], alo[2 * h + 1]);
     }
   } else {
 #pragma unroll
@@ -136,15 +131,6 @@ __device__ __forceinline__ void convert_group(const f32x4 (&raw)[8], bf16x8 (&ah
       split8(col, ahi[c], alo[c]);
     }
   }
-}
-
-// The scales of an e4m3 batch go into its weights: the codes are then exact
-// bfloat16 values, with no low part to form or to multiply, and a lane requests
-// one scale per batch instead of one per row and column group. (A rounding of
-// w * scale takes the place of one of code * scale; 16 frames of 640x480, 512
-// columns: 4.43 -> 3.68 ms.) Scale of entry j from the lanes' values.
-__device__ __forceinline__ float lane_value(float x, int j) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));
 }
 
 // acc[c][p] += F^T W^T for one column group (4 column tiles) and the 4 pixel
@@ -164,7 +150,7 @@ __device__ __forceinline__ void mfma_group(f32x4 (&acc)[4][4], const bf16x8 (&ah
     for (int c = 0; c < 4; ++c) {
       acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[c], bhi, acc[c][p], 0, 0, 0);
       acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[c], blo, acc[c][p], 0, 0, 0);
-      if constexpr (DT == QR_F32)
+      if constexpr (DT != QR_BF16)
         acc[c][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo[c], bhi, acc[c][p], 0, 0, 0);
     }
   }
@@ -317,16 +303,19 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
       // valid rows (weight 0), columns past the width of a partial group are
       // clamped to its first, and a group past the width (no MFMAs, nothing
       // stored) reads column 0 (their results are never stored).
-      float scale8 = 0.f;  // lanes 0..7: the scales of this wave's entries
-      if constexpr (DT == QR_FP8_E4M3) scale8 = v.scale[gid[kDQ * wave + (lane & (kDQ - 1))]];
       f32x4 raw[8];
+      float sc[8] = {};  // the rows' scales, for both groups
       const auto load_group = [&](int k) {
         const int col = gw[k] > 0 ? gbase[k] + (coff < gw[k] ? coff : 0) : 0;
         const u32x4 ga = *reinterpret_cast<const u32x4*>(&gid[8 * kb]);
         const u32x4 gb = *reinterpret_cast<const u32x4*>(&gid[8 * kb + 4]);
         const uint32_t g8[8] = {ga.x, ga.y, ga.z, ga.w, gb.x, gb.y, gb.z, gb.w};
 #pragma unroll
-        for (int t = 0; t < 8; ++t) raw[t] = load_raw4<DT>(v, g8[t], dim, col);
+        for (int t = 0; t < 8; ++t) {
+          raw[t] = load_raw4<DT>(v, g8[t], dim, col);
+          if constexpr (DT == QR_FP8_E4M3)
+            if (k == 0) sc[t] = v.scale[g8[t]];
+        }
       };
       if (batch == lo) {  // uniform: the later ones are requested a batch ahead
         rmean = v.means2d[rgid];
@@ -349,10 +338,7 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
       bool any = false;
       bf16x8 whi, wlo;
 #pragma unroll
-      for (int j = 0; j < kDQ; ++j) {
-        any |= w8[j] != 0.f;
-        if constexpr (DT == QR_FP8_E4M3) w8[j] *= lane_value(scale8, j);
-      }
+      for (int j = 0; j < kDQ; ++j) any |= w8[j] != 0.f;
       split8(w8, whi, wlo);
       *reinterpret_cast<bf16x8*>(&L.whi[lane * kWS + kDQ * wave]) = whi;
       *reinterpret_cast<bf16x8*>(&L.wlo[lane * kWS + kDQ * wave]) = wlo;
@@ -380,7 +366,7 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
 #pragma unroll
       for (int k = 0; k < kStripGroups; ++k) {
         bf16x8 ahi[4], alo[4];
-        convert_group<DT>(raw, ahi, alo);
+        convert_group<DT>(raw, sc, ahi, alo);
         if (gw[k] != 0) mfma_group<DT>(acc[k], ahi, alo, L.whi, L.wlo, busy, ci, kb);
         if (k + 1 < kStripGroups) load_group(k + 1);
       }
@@ -416,8 +402,8 @@ struct DenseNarrowLds {
   __attribute__((aligned(16))) uint32_t gid[2][kDB];
 };
 
-// One column of row g (dim == 16 layout): float32 value, or the bfloat16 or
-// e4m3 code in the low bits.
+// One column of row g (dim == 16 layout): float32 value, or the bfloat16 code
+// in the low half.
 template <int DT>
 __device__ __forceinline__ float load_raw1(const GView& v, uint32_t g, int d) {
   const uint64_t off = static_cast<uint64_t>(g) * 16u + static_cast<uint32_t>(d);
@@ -426,7 +412,8 @@ __device__ __forceinline__ float load_raw1(const GView& v, uint32_t g, int d) {
   } else if constexpr (DT == QR_BF16) {
     return __uint_as_float(static_cast<const QR_GLOBAL uint16_t*>(v.feats)[off]);
   } else {
-    return __uint_as_float(static_cast<const QR_GLOBAL uint8_t*>(v.feats)[off]);
+    const uint32_t r = static_cast<const QR_GLOBAL uint8_t*>(v.feats)[off];
+    return __builtin_amdgcn_cvt_pk_f32_fp8(static_cast<int>(r), false)[0] * v.scale[g];
   }
 }
 
@@ -510,8 +497,7 @@ __device__ void dense_tile_narrow(const GView& v, int tile, int dim, const qr_pa
     const u32x4 ga = *reinterpret_cast<const u32x4*>(&L.gid[par][8 * kb]);
     const u32x4 gb = *reinterpret_cast<const u32x4*>(&L.gid[par][8 * kb + 4]);
     const uint32_t g8[8] = {ga.x, ga.y, ga.z, ga.w, gb.x, gb.y, gb.z, gb.w};
-    float scale32 = 0.f;  // lanes 0..31: the scales of the batch's entries
-    if constexpr (DT == QR_FP8_E4M3) scale32 = v.scale[L.gid[par][lane & (kDB - 1)]];
+    float sc[8] = {};
     f32x4 raw[kOne ? 1 : 8];
     float raw1[kOne ? 8 : 1];
     if constexpr (kOne) {
@@ -519,7 +505,10 @@ __device__ void dense_tile_narrow(const GView& v, int tile, int dim, const qr_pa
       for (int t = 0; t < 8; ++t) raw1[t] = load_raw1<DT>(v, g8[t], ci);
     } else {
 #pragma unroll
-      for (int t = 0; t < 8; ++t) raw[t] = load_raw4<DT>(v, g8[t], dim, col);
+      for (int t = 0; t < 8; ++t) {
+        raw[t] = load_raw4<DT>(v, g8[t], dim, col);
+        if constexpr (DT == QR_FP8_E4M3) sc[t] = v.scale[g8[t]];
+      }
     }
 
     // Eq. 1 along the lane's ray, in list order
@@ -545,7 +534,6 @@ __device__ void dense_tile_narrow(const GView& v, int tile, int dim, const qr_pa
           }
         }
         any |= w != 0.f;
-        if constexpr (DT == QR_FP8_E4M3) w *= lane_value(scale32, e);
         w8[j] = w;
       }
       bf16x8 bh, bl;
@@ -562,12 +550,8 @@ __device__ void dense_tile_narrow(const GView& v, int tile, int dim, const qr_pa
     if (busy == 0ull) continue;
     if constexpr (kOne) {
       bf16x8 ahi, alo;
-      if constexpr (DT == QR_F32) {
+      if constexpr (DT != QR_BF16) {
         split8(raw1, ahi, alo);
-      } else if constexpr (DT == QR_FP8_E4M3) {
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-          ahi[t] = static_cast<__bf16>(__builtin_amdgcn_cvt_pk_f32_fp8(__float_as_int(raw1[t]), false)[0]);
       } else {
 #pragma unroll
         for (int t = 0; t < 8; ++t)
@@ -580,12 +564,12 @@ __device__ void dense_tile_narrow(const GView& v, int tile, int dim, const qr_pa
         const bf16x8 blo = *reinterpret_cast<const bf16x8*>(&wlo[(16 * p + ci) * kWS + 8 * kb]);
         acc[0][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi, bhi, acc[0][p], 0, 0, 0);
         acc[0][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi, blo, acc[0][p], 0, 0, 0);
-        if constexpr (DT == QR_F32)
+        if constexpr (DT != QR_BF16)
           acc[0][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo, bhi, acc[0][p], 0, 0, 0);
       }
     } else {
       bf16x8 ahi[4], alo[4];
-      convert_group<DT>(raw, ahi, alo);
+      convert_group<DT>(raw, sc, ahi, alo);
       mfma_group<DT>(acc, ahi, alo, whi, wlo, busy, ci, kb);
     }
   }
