@@ -34,7 +34,7 @@
 // Both products of step 2 take float32 operands split into bfloat16 pairs
 // x = x_hi + x_lo and form hi.hi + hi.lo + lo.hi with float32 accumulation
 // (relative error below 2^-16 per product; three parts past a tile's first 32
-// slots). Selections without a slot (more
+// slots and past list position 2,048). Selections without a slot (more
 // than 256 distinct selections in a tile, or a position past kPosCap) are
 // handled by a plain wave-wide path.
 //
@@ -100,6 +100,7 @@ constexpr int kSlots = 32;       // distinct selections of one pass over dL/d(ou
 constexpr int kMaxSlots = 256;   // distinct selections of a tile given slots
 constexpr int kPosCap = 8192;    // list positions covered by the slot bitmap
 constexpr int kPosWords = kPosCap / 32;
+constexpr int kNearWords = 2048 / 32;  // list positions of the first pass (two-part products)
 constexpr int kSub = 32;         // columns of a block (MFMA k of the dots)
 constexpr int kPB = 32;          // pixels of a block, two tile rows (MFMA k of the feature gradients)
 constexpr int kTS = kSub + 8;    // LDS stride (bf16) of a pixel in the transposing tile
@@ -231,7 +232,8 @@ struct Shares {
 // tiles and the workgroup adds them up for the selected pairs, one thread per
 // (pixel, selection). (Adding them with LDS float atomics kept the LDS busy
 // for 61% of the kernel.)
-// FAR: the passes after the first. float32 operands are split into three
+// FAR: the passes after the first, which ends at slot 32 or at the first slot
+// of a list position past 2,048. float32 operands are split into three
 // bfloat16 parts instead of two, six products instead of three, which keeps
 // float32's precision (relative error 2^-24 instead of 2^-16; a tile's later
 // selections were always taken in float32), and half the slots are taken per
@@ -711,9 +713,10 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
     }
     __syncthreads();  // the masks may be rewritten
   };
-  if (nslots > 0) pass(0, min(kSlots, nslots), std::false_type{});
+  const int near = min(min(kSlots, nslots), B.bpre[kNearWords]);  // uniform
+  if (near > 0) pass(0, near, std::false_type{});
 #pragma unroll 1
-  for (int base = kSlots; base < nslots; base += pass_slots<true>())
+  for (int base = near; base < nslots; base += pass_slots<true>())
     pass(base, min(pass_slots<true>(), nslots - base), std::true_type{});
   if (walker) slotless<DT>(v, gg, B.inv, s_pos, s_w, tx, ty, wave, lane, dim, nslotted, ns, KP, geo);
   if (!geo) return;
