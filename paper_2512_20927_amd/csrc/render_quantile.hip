@@ -131,12 +131,16 @@ __device__ __forceinline__ void gather_group(const GView& v, const int* ug, cons
 // kNarrowRows (16) row loads of a lane are requested before the first is used
 // (slots past a group's distinct count load a row of the group again and are
 // not accumulated). One memory round trip per round and 16 rows instead of
-// several per group. ug, uw: the wave's groups, `cap` entries each;
+// several per group. ug, uw, um: the wave's groups, `cap` entries each;
 // count(g): distinct selections of the wave's group g, negative: skip it.
+// A pixel takes every row of its group, with weight 0 where it did not select
+// it; a lane whose result is not finite forms it again from the selected rows
+// alone, so that such a row reaches no pixel that did not select it.
 constexpr int kNarrowRows = 16;
 
 template <int DT, int OT, class Count>
-__device__ __forceinline__ void gather_groups_narrow(const GView& v, const int* ug, const float4* uw, int cap,
+__device__ __forceinline__ void gather_groups_narrow(const GView& v, const int* ug, const float4* uw,
+                                                     const uint8_t* um, int cap,
                                                      const Count& count, int wave, int tx, int ty,
                                                      int lane, int dim) {
   const int dim4 = dim >> 2;
@@ -169,6 +173,27 @@ __device__ __forceinline__ void gather_groups_narrow(const GView& v, const int* 
               a[q].w += ws[q] * f[e].w;
             }
           }
+        }
+      }
+    }
+    float sum = 0.f;
+#pragma unroll
+    for (int q = 0; q < kPG; ++q) sum += (a[q].x + a[q].y) + (a[q].z + a[q].w);
+    if (!(fabsf(sum) < INFINITY)) {
+#pragma unroll
+      for (int q = 0; q < kPG; ++q) a[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+      for (int e = grp * cap; e < grp * cap + nu; ++e) {
+        const float4 f = load_feat4_global<DT>(v.feats, v.scale, ug[e], dim, 4 * cl);
+        const float4 w = uw[e];
+        const float ws[kPG] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int q = 0; q < kPG; ++q) {
+          if (!((um[e] >> q) & 1)) continue;
+          a[q].x += ws[q] * f.x;
+          a[q].y += ws[q] * f.y;
+          a[q].z += ws[q] * f.z;
+          a[q].w += ws[q] * f.w;
         }
       }
     }
@@ -336,7 +361,7 @@ __device__ __forceinline__ void topk_tile(const GView& v, int tile, int K, int d
   const int wave = tid >> 6;
   const int g0 = wave * kWaveGroups;
   if (dim <= 128) {
-    gather_groups_narrow<DT, OT>(v, &L.ugid[g0 * UCAP], &L.uw[g0 * UCAP], UCAP,
+    gather_groups_narrow<DT, OT>(v, &L.ugid[g0 * UCAP], &L.uw[g0 * UCAP], &L.umask[g0 * UCAP], UCAP,
                                  [&](int g) { return L.unum[g0 + g]; }, wave, tx, ty, lane, dim);
     gather_groups_narrow_overflow<DT, OT>(v, L, s_sel_pos, s_sel_w, KP, K, wave, tx, ty, lane, dim);
   } else {
@@ -410,7 +435,7 @@ __device__ __forceinline__ void quantile_tile(const GView& v, int tile, int K, i
   int cnt;
   const PixelSel sel = collect(t.inside, lg * kGroupCap, kGroupCap, t.inside && sel_gid_out, cnt);
   if (dim <= 128) {
-    gather_groups_narrow<DT, OT>(v, ug, uw, kGroupCap,
+    gather_groups_narrow<DT, OT>(v, ug, uw, um, kGroupCap,
                                  [&](int g) {
                                    const int n = __shfl(cnt, 4 * g, 64);
                                    return n > kGroupCap ? -1 : n;
