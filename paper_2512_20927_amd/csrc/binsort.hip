@@ -190,7 +190,9 @@ static void scan_exclusive(const uint32_t* in, uint32_t* out, int64_t n, uint32_
 // ---- bucket by tile: counters in LDS -----------------------------------------
 // The pairs of 64 consecutive records of a view, called by a whole wave: a
 // lane visits the tiles of its own record if there are at most kOwnTiles (no
-// division, 64 records side by side); the records with more are visited one
+// division, 64 records side by side; neighbouring lanes start from different
+// corners, so that records of one rectangle meet less on its counters: 4,096
+// records over all of 16 tiles, 207 us from one corner, 141 from four); the records with more are visited one
 // after the other, their tiles spread over the 64 lanes, so a Gaussian that
 // covers a thousand tiles costs sixteen lane-rounds instead of a thousand
 // serial iterations of one thread. (All records one after the other: 68 and
@@ -205,12 +207,14 @@ __device__ __forceinline__ void for_pairs(uint32_t cnt, const int4& r, uint32_t 
   const int lane = threadIdx.x & 63;
   if (cnt <= kOwnTiles) {
     const unsigned long long key = (static_cast<unsigned long long>(d) << 32) | id;
-    int t = r.y * tiles_x + r.x, x = r.x;
+    const int w = r.z - r.x, dx = lane & 1 ? -1 : 1;
+    const int next_row = (lane & 2 ? -tiles_x : tiles_x) - dx * (w - 1);
+    int t = (lane & 2 ? r.w - 1 : r.y) * tiles_x + (lane & 1 ? r.z - 1 : r.x), left = w;
     for (uint32_t k = 0; k < cnt; ++k) {
       pair(t, key);
-      const bool wrap = ++x == r.z;
-      t += wrap ? tiles_x - (r.z - r.x) + 1 : 1;
-      x = wrap ? r.x : x;
+      const bool wrap = --left == 0;
+      t += wrap ? next_row : dx;
+      left = wrap ? w : left;
     }
   }
   for (uint64_t todo = __ballot(cnt > kOwnTiles); todo; todo &= todo - 1) {
@@ -226,25 +230,37 @@ __device__ __forceinline__ void for_pairs(uint32_t cnt, const int4& r, uint32_t 
   }
 }
 
-// Records [first, last) of a view, by a workgroup of kWideThreads. The next
-// records' tile counts are requested before the current ones are visited.
-template <bool kDepth, class Pair>
-__device__ __forceinline__ void for_records(int64_t base, int64_t first, int64_t last,
-                                            const int4* __restrict__ rect, const uint32_t* __restrict__ touched,
-                                            const float* __restrict__ depth, int tiles_x, const Pair& pair) {
+// Records [first, last) by a workgroup of kWideThreads. The next records' tile
+// counts are requested before the current ones are visited. place(i, r): the
+// id in record i's keys; may move its rectangle.
+template <bool kDepth, class Place, class Pair>
+__device__ __forceinline__ void for_records(int64_t first, int64_t last, const int4* __restrict__ rect,
+                                            const uint32_t* __restrict__ touched, const float* __restrict__ depth,
+                                            int tiles_x, const Place& place, const Pair& pair) {
   int64_t i = first + threadIdx.x;
-  uint32_t next = i < last ? touched[base + i] : 0u;
+  uint32_t next = i < last ? touched[i] : 0u;
   for (int64_t w0 = first + (threadIdx.x & ~63); w0 < last; w0 += kWideThreads, i += kWideThreads) {
     const uint32_t cnt = next;
-    next = i + kWideThreads < last ? touched[base + i + kWideThreads] : 0u;
+    next = i + kWideThreads < last ? touched[i + kWideThreads] : 0u;
     int4 r = make_int4(0, 0, 0, 0);
-    uint32_t d = 0;
+    uint32_t d = 0, id = 0;
     if (cnt) {
-      r = rect[base + i];
-      if (kDepth) d = __float_as_uint(depth[base + i]);
+      r = rect[i];
+      if (kDepth) d = __float_as_uint(depth[i]);
+      id = place(i, r);
     }
-    for_pairs(cnt, r, d, static_cast<uint32_t>(i), tiles_x, pair);
+    for_pairs(cnt, r, d, id, tiles_x, pair);
   }
+}
+
+// The records of chunk c of a view.
+template <bool kDepth, class Pair>
+__device__ __forceinline__ void for_chunk(int64_t view, int64_t n_per_view, int64_t c, int64_t chunk,
+                                          const int4* __restrict__ rect, const uint32_t* __restrict__ touched,
+                                          const float* __restrict__ depth, int tiles_x, const Pair& pair) {
+  const int64_t base = view * n_per_view;
+  for_records<kDepth>(base + c * chunk, base + min((c + 1) * chunk, n_per_view), rect, touched, depth, tiles_x,
+                      [&](int64_t i, int4&) { return static_cast<uint32_t>(i - base); }, pair);
 }
 
 // Workgroup b takes chunk b % n_chunks of view b / n_chunks. counts:
@@ -257,8 +273,8 @@ chunk_count_kernel(int64_t n_per_view, int n_chunks, int64_t chunk, const int4* 
   for (int t = threadIdx.x; t < n_tiles; t += kWideThreads) h[t] = 0u;
   __syncthreads();
   const int64_t view = blockIdx.x / n_chunks, c = blockIdx.x % n_chunks;
-  for_records<false>(view * n_per_view, c * chunk, min((c + 1) * chunk, n_per_view), rect, touched, nullptr, tiles_x,
-                     [&](int t, unsigned long long) { atomicAdd(&h[t], 1u); });
+  for_chunk<false>(view, n_per_view, c, chunk, rect, touched, nullptr, tiles_x,
+                   [&](int t, unsigned long long) { atomicAdd(&h[t], 1u); });
   __syncthreads();
   uint32_t* const out = counts + static_cast<int64_t>(blockIdx.x) * n_tiles;
   for (int t = threadIdx.x; t < n_tiles; t += kWideThreads) out[t] = h[t];
@@ -306,33 +322,42 @@ chunk_scatter_kernel(int64_t n_per_view, int n_chunks, int64_t chunk, const int4
   const uint32_t* const before = counts + static_cast<int64_t>(blockIdx.x) * n_tiles;
   for (int t = threadIdx.x; t < n_tiles; t += kWideThreads) h[t] = offsets[view * n_tiles + t] + before[t];
   __syncthreads();
-  for_records<true>(view * n_per_view, c * chunk, min((c + 1) * chunk, n_per_view), rect, touched, depth, tiles_x,
-                    [&](int t, unsigned long long key) {
-                      const int64_t slot = atomicAdd(&h[t], 1u);
-                      if (slot < capacity) bucket[slot] = key;
-                    });
+  for_chunk<true>(view, n_per_view, c, chunk, rect, touched, depth, tiles_x, [&](int t, unsigned long long key) {
+    const int64_t slot = atomicAdd(&h[t], 1u);
+    if (slot < capacity) bucket[slot] = key;
+  });
 }
 
 // Small scenes: count, scan and scatter in one workgroup and one launch (1,000
-// Gaussians on 16 tiles: 4.7 us against 14.5 us in four launches). The limit
-// on records times tiles keeps it to a few records per thread on a small grid,
-// and to few records on a large one.
+// Gaussians on 16 tiles: 4.7 us against 14.5 us in four launches). The records
+// of all views are taken side by side, whatever their number (view after view
+// cost a memory round trip for each: 64 views of 64 on 16 tiles, 80 us, now 16;
+// 1,024 of 16 on 4 tiles, 730 and 27). The limits on records and on records
+// times tiles keep it to a few records per thread on a small grid, and to few
+// records on a large one (65,536 records in 4,096 one-tile views: 78 us here,
+// 36 in chunks).
 constexpr int kSmallTiles = 4 * kWideThreads;  // four tiles per thread in the scan
 constexpr int64_t kSmallWork = 1 << 16;  // records times tiles of a view
+constexpr int64_t kSmallRecords = 16 * kWideThreads;
 __global__ void __launch_bounds__(kWideThreads)
-bucket_small_kernel(int n_views, int64_t n_per_view, const int4* __restrict__ rect,
-                    const uint32_t* __restrict__ touched, const float* __restrict__ depth, int tiles_x,
-                    int n_tiles, int64_t capacity, uint32_t* __restrict__ tile_offsets,
-                    uint32_t* __restrict__ total_pairs, unsigned long long* __restrict__ bucket) {
+bucket_small_kernel(int n, int n_per_view, const int4* __restrict__ rect, const uint32_t* __restrict__ touched,
+                    const float* __restrict__ depth, int tiles_x, int tiles_y, int all, int64_t capacity,
+                    uint32_t* __restrict__ tile_offsets, uint32_t* __restrict__ total_pairs,
+                    unsigned long long* __restrict__ bucket) {
   __shared__ uint32_t h[kSmallTiles];
   __shared__ uint32_t lds16[16];
   for (int t = threadIdx.x; t < kSmallTiles; t += kWideThreads) h[t] = 0u;
   __syncthreads();
-  for (int v = 0; v < n_views; ++v)
-    for_records<false>(v * n_per_view, 0, n_per_view, rect, touched, nullptr, tiles_x,
-                       [&](int t, unsigned long long) { atomicAdd(&h[v * n_tiles + t], 1u); });
+  const auto place = [&](int64_t i, int4& r) {  // into the stacked grid of all views
+    const int view = static_cast<int>(i) / n_per_view;
+    r.y += view * tiles_y;
+    r.w += view * tiles_y;
+    return static_cast<uint32_t>(static_cast<int>(i) - view * n_per_view);
+  };
+  for_records<false>(0, n, rect, touched, nullptr, tiles_x, place,
+                     [&](int t, unsigned long long) { atomicAdd(&h[t], 1u); });
   __syncthreads();
-  const int all = n_views * n_tiles, t0 = 4 * threadIdx.x;
+  const int t0 = 4 * threadIdx.x;
   uint32_t c[4];
   uint32_t s = 0, total;
 #pragma unroll
@@ -353,12 +378,10 @@ bucket_small_kernel(int n_views, int64_t n_per_view, const int4* __restrict__ re
   }
   if (capacity == 0) return;
   __syncthreads();
-  for (int v = 0; v < n_views; ++v)
-    for_records<true>(v * n_per_view, 0, n_per_view, rect, touched, depth, tiles_x,
-                      [&](int t, unsigned long long key) {
-                        const int64_t slot = atomicAdd(&h[v * n_tiles + t], 1u);
-                        if (slot < capacity) bucket[slot] = key;
-                      });
+  for_records<true>(0, n, rect, touched, depth, tiles_x, place, [&](int t, unsigned long long key) {
+    const int64_t slot = atomicAdd(&h[t], 1u);
+    if (slot < capacity) bucket[slot] = key;
+  });
 }
 
 // ---- bucket by tile: counters in global memory --------------------------------
@@ -720,9 +743,10 @@ static int bin_sort_impl(const char* name, void* stream, int64_t n_views, int64_
   n_chunks = std::max<int64_t>(std::min<int64_t>(n_chunks, ceil_div(512, n_views)), 1);
   n_chunks = std::min(n_chunks, static_cast<int64_t>(sizeof(uint64_t)) * capacity /
                                     (n_tiles * static_cast<int64_t>(sizeof(uint32_t))));
-  if (n > 0 && n_tiles <= kSmallTiles && n * view_tiles <= kSmallWork) {
-    hipLaunchKernelGGL(bucket_small_kernel, dim3(1), dim3(kWideThreads), 0, s, static_cast<int>(n_views), n_per_view,
-                       rect, tiles_touched, depth, tiles_x, view_tiles, capacity, tile_offsets, total_pairs, bucket);
+  if (n > 0 && n_tiles <= kSmallTiles && n <= kSmallRecords && n * view_tiles <= kSmallWork) {
+    hipLaunchKernelGGL(bucket_small_kernel, dim3(1), dim3(kWideThreads), 0, s, static_cast<int>(n),
+                       static_cast<int>(n_per_view), rect, tiles_touched, depth, tiles_x, tiles_y,
+                       static_cast<int>(n_tiles), capacity, tile_offsets, total_pairs, bucket);
   } else if (n > 0 && view_tiles <= kLdsTiles && n_chunks > 0) {
     const int64_t chunk = ceil_div(n_per_view, n_chunks);
     const unsigned blocks = static_cast<unsigned>(n_views * n_chunks);
