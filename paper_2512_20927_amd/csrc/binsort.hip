@@ -386,7 +386,7 @@ bucket_small_kernel(int n, int n_per_view, const int4* __restrict__ rect, const 
 
 // ---- bucket by tile: counters in global memory --------------------------------
 // For grids whose counters do not fit in LDS, or workspaces without room for
-// the chunks' counts.
+// enough chunks' counts.
 __global__ void __launch_bounds__(256)
 zero_u32_kernel(uint32_t* __restrict__ a, int64_t n) {
   for (int64_t i = blockIdx.x * 256LL + threadIdx.x; i < n; i += 256LL * gridDim.x) a[i] = 0u;
@@ -738,16 +738,20 @@ static int bin_sort_impl(const char* name, void* stream, int64_t n_views, int64_
   // Chunks of at least 1,024 records (one per thread: with 4,096, 60k records
   // occupy 15 CUs), and no more workgroups than fill the chip (512 of 16
   // waves). Their counts lie where long buckets are sorted later, which bounds
-  // their number by the capacity.
-  int64_t n_chunks = std::min<int64_t>(ceil_div(n_per_view, kWideThreads), kMaxChunks);
-  n_chunks = std::max<int64_t>(std::min<int64_t>(n_chunks, ceil_div(512, n_views)), 1);
-  n_chunks = std::min(n_chunks, static_cast<int64_t>(sizeof(uint64_t)) * capacity /
-                                    (n_tiles * static_cast<int64_t>(sizeof(uint32_t))));
+  // their number by the capacity: with room for less than a third of the chunks
+  // each workgroup takes too many records one after the other, and the global
+  // counters are as fast or faster, as there are few pairs then (1M records,
+  // 81 x 61 tiles: room for 2 chunks 268 us in chunks, 24 by global counters;
+  // for 45, 52 and 36; for 90, 46 and 48; for 170, 42 and 69).
+  const int64_t want = std::max<int64_t>(
+      std::min(std::min<int64_t>(ceil_div(n_per_view, kWideThreads), kMaxChunks), ceil_div(512, n_views)), 1);
+  const int64_t n_chunks = std::min(want, static_cast<int64_t>(sizeof(uint64_t)) * capacity /
+                                              (n_tiles * static_cast<int64_t>(sizeof(uint32_t))));
   if (n > 0 && n_tiles <= kSmallTiles && n <= kSmallRecords && n * view_tiles <= kSmallWork) {
     hipLaunchKernelGGL(bucket_small_kernel, dim3(1), dim3(kWideThreads), 0, s, static_cast<int>(n),
                        static_cast<int>(n_per_view), rect, tiles_touched, depth, tiles_x, tiles_y,
                        static_cast<int>(n_tiles), capacity, tile_offsets, total_pairs, bucket);
-  } else if (n > 0 && view_tiles <= kLdsTiles && n_chunks > 0) {
+  } else if (n > 0 && view_tiles <= kLdsTiles && 3 * n_chunks >= want) {
     const int64_t chunk = ceil_div(n_per_view, n_chunks);
     const unsigned blocks = static_cast<unsigned>(n_views * n_chunks);
     const size_t lds = sizeof(uint32_t) * static_cast<size_t>(view_tiles);

@@ -54,3 +54,19 @@ def test_many_small_views_are_taken_side_by_side(qr, nv, n, tx, ty):
     us, gid, offs = _timed(qr, views, tx, ty, 4 * nv * n)
     _check(views, tx, ty, gid, offs)
     assert us <= 300.0, us  # view after view: 2,960 us for 4,096 views, 730 for 1,024
+
+
+@pytest.mark.parametrize("n,tx,ty,visible,room", [(1_000_000, 81, 61, 1000, 1.0), (1_000_000, 81, 61, 1000, 2.0),
+                                                  (200_000, 40, 30, 500, 1.25), (1_000_000, 81, 61, 100_000, 1.25)])
+def test_a_small_capacity_leaves_no_long_chunks(qr, n, tx, ty, visible, room):
+    """Few visible records of many: the workspace, sized by the pairs, has no
+    room for the counts of enough chunks."""
+    rect, depth = _records(n, tx, ty, 2, n)
+    keep = torch.randperm(n, generator=torch.Generator().manual_seed(visible))[:visible]
+    hidden = torch.ones(n, dtype=torch.bool)
+    hidden[keep] = False
+    rect[hidden] = 0
+    pairs = int(((rect[:, 2] - rect[:, 0]) * (rect[:, 3] - rect[:, 1])).sum())
+    us, gid, offs = _timed(qr, [(rect, depth)], tx, ty, int(pairs * room))
+    _check([(rect, depth)], tx, ty, gid[:pairs], offs)
+    assert us <= 150.0, us  # one chunk: 800 us for the first
