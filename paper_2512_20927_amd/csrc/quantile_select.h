@@ -64,16 +64,15 @@ struct TopkLds {
 // LDS of one Q-Render workgroup: record staging, thresholds and the groups'
 // distinct selections as the walk collects them. The size does not depend on
 // K (the pixels' lists took 8 K bytes each and left room for one workgroup per
-// CU at K = 40): three workgroups fit a CU's 160 KB at any K. Groups with
-// more than kGroupCap distinct selections (0.5% of the groups of a room at K =
-// 40, none at K = 8) are collected in further walks of the tile, two groups of
-// a wave at a time in the whole wave's space: kRedoCap = 256 entries each, as
-// many as four pixels can select.
+// CU at K = 40): three workgroups fit a CU's 160 KB at any K. A group that
+// would need more than kGroupCap entries (0.5% of the groups of a room at K =
+// 40, none at K = 8; most groups of a scene of pixel-sized, faint Gaussians)
+// pauses there, its entries are gathered, and the walk goes on from where the
+// first group paused.
 constexpr int kGroupCap = 32;
 constexpr int kWaveGroups = kGroups / 4;
-constexpr int kRedoGroups = 2;
-constexpr int kRedoCap = kGroupCap * kWaveGroups / kRedoGroups;
-static_assert(kRedoCap >= kPG * QR_MAX_K, "a collected group always fits");
+constexpr int kWaveCap = kWaveGroups * kGroupCap;
+static_assert(kWaveCap >= kPG * QR_MAX_K, "a group's selections always fit a wave's space");
 
 struct QuantileLds {
   static constexpr bool kKeepIds = true;
@@ -87,6 +86,7 @@ struct QuantileLds {
   float4 uw[kGroups * kGroupCap];          // weights of the entries for their group's four pixels
   int ugid[kGroups * kGroupCap];           // Gaussian ids
   uint8_t umask[kGroups * kGroupCap];      // bit q: pixel q of the group selected the entry
+  int go_on;                               // list position where the next walk starts
 };
 static_assert(3 * ((sizeof(QuantileLds) + 64 + 1279) / 1280) * 1280 <= 160 * 1024, "three workgroups per CU");
 
@@ -139,6 +139,15 @@ __device__ __forceinline__ ViewArgs view_args(const qr_view& qv) {
                   qv.feature_scale, qv.out, qv.T_q, qv.n_sel};
 }
 
+// A pixel's walk between two passes over the list.
+constexpr int kWalkDone = 0x7fffffff;
+struct WalkState {
+  float T = 1.f, TQ = 1.f;
+  int k = 0, last = 0;
+  int from = kWalkDone;  // the entry it goes on from, kWalkDone: none
+  double mu = 0.0, sigma = 0.0;  // Stratified-K
+};
+
 // What the walk leaves in registers for the calling thread's pixel.
 struct PixelSel {
   int ns;    // selections (0 outside the image)
@@ -156,6 +165,7 @@ struct ListSink {
   int* __restrict__ my_pos;
   float* __restrict__ my_w;
   int ns = 0;
+  static constexpr bool kPauses = false;
   // sel: lane mask of the pixels that selected list position pos
   __device__ __forceinline__ void add(uint64_t sel, float w, int pos, int) {
     if (!__builtin_amdgcn_inverse_ballot_w64(sel)) return;
@@ -166,8 +176,12 @@ struct ListSink {
 };
 
 // The distinct selections of the lane's group of four pixels. Called with
-// all lanes of the wave (the four lanes of a group count alike).
+// all lanes of the wave (the four lanes of a group count alike). Entries past
+// the capacity are counted and not kept; kPause: the walk lets a full group
+// pause instead.
+template <bool kPause>
 struct GroupSink {
+  static constexpr bool kPauses = kPause;
   float* __restrict__ uw;        // the lane's pixel's weight of the group's first entry
   int* __restrict__ ugid;
   uint8_t* __restrict__ umask;
@@ -242,16 +256,21 @@ constexpr int kCmpLt = 4, kCmpNotLt = 11;  // a < b; !(a < b)
 // their sum (in a ListSink, whose entries it replaces). A pixel is done
 // once its list is full and T alpha_max is no larger than the smallest kept
 // weight: no later weight can exceed it.
-template <int MODE, class WalkLds, class Sink>
-__device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi, int K, float pxc,
+// A group whose sink is full pauses at the next entry on a ray of its pixels:
+// their st.from is that entry. (Such groups' thresholds are raised, so that
+// entries cross them, and only crossings pay for the check: checked at every
+// entry it cost the walk 4%.) kResume: the pixels with such an entry go on from
+// there, over the entries from `start` (the first of them) on.
+template <int MODE, bool kResume, class WalkLds, class Sink>
+__device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int start, int hi, int K, float pxc,
                                                   float pyc, bool inside, const qr_params& prm,
-                                                  WalkLds& L, Sink& sink) {
+                                                  WalkLds& L, Sink& sink, WalkState& st) {
   const int tid = threadIdx.x;
   // thr[k] = t_{k+1}; thr[K] = 0 (identical for every tile of a launch)
-  if constexpr (MODE == QR_SELECT_QUANTILE) {
+  if constexpr (MODE == QR_SELECT_QUANTILE && !kResume) {
     if (tid <= K) L.thr[tid] = quantile_threshold(tid + 1, K);
   }
-  if constexpr (MODE == QR_SELECT_STRATIFIED) {
+  if constexpr (MODE == QR_SELECT_STRATIFIED && !kResume) {
     if (tid < K) L.zq[tid] = stratified_z(tid + 1, K);  // read after the barrier below
     __syncthreads();
   }
@@ -297,8 +316,8 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
     return any;
   };
 
-  double mu = 0.0, sigma = 0.0;
-  if constexpr (MODE == QR_SELECT_STRATIFIED) {
+  double &mu = st.mu, &sigma = st.sigma;
+  if constexpr (MODE == QR_SELECT_STRATIFIED && !kResume) {
     double s1 = 1.0, s2 = 1.0;  // T_0 = 1
     int n = 1;
     float T1 = 1.f;
@@ -338,17 +357,20 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
     else return -1.f;  // Top-K has none
   };
 
-  float T = 1.f, TQ = 1.f;
-  int k = 0, last = 0, staged = lo;
-  uint64_t live = wave_ballot(inside);  // pixels whose walk has not ended
+  float T = st.T, TQ = st.TQ;
+  int k = st.k, last = st.last, staged = start;
+  const int from = st.from;
+  st.from = kWalkDone;
+  uint64_t live = wave_ballot(kResume ? from != kWalkDone : inside);  // pixels whose walk has not ended
+  uint64_t full = 0ull;  // lanes of groups whose sink is full
   // t_{k+1}: changes only at a crossing
   float thr_k;
-  if constexpr (MODE == QR_SELECT_STRATIFIED) thr_k = threshold(0);
+  if constexpr (kResume || MODE == QR_SELECT_STRATIFIED) thr_k = threshold(k);
   else thr_k = quantile_threshold(1, K);
   float wmin = 0.f;  // Top-K: the worst kept entry (smallest weight, later position among equals)
   int imin = 0;
 
-  for (int batch = lo; batch < hi; batch += kTilePix) {
+  for (int batch = start; batch < hi; batch += kTilePix) {
     if (__syncthreads_or(live != 0ull) == 0) break;
     staged = batch;
     stage(batch);
@@ -361,10 +383,11 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
         uint64_t on = touch[u] & live;  // not finished, and on this pixel's ray
+        const int pos = batch + j + u;
+        if constexpr (kResume) on &= wave_ballot(pos >= from);
         if (on == 0ull) continue;
         const float alpha = oG[u] >= amax ? amax : oG[u];
         const float T_test = T * (1.f - alpha);
-        const int pos = batch + j + u;
         if constexpr (MODE != QR_SELECT_QUANTILE) {  // the dense blend stops before this Gaussian
           const uint64_t stop = __builtin_amdgcn_fcmpf(T_test, prm.T_eps, kCmpLt) & on;
           live &= ~stop;
@@ -406,10 +429,20 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
           }
         } else {
           // a quantile Gaussian of the pixel
-          const uint64_t cross = __builtin_amdgcn_fcmpf(T_test, thr_k, kCmpLt) & on;
+          uint64_t cross = __builtin_amdgcn_fcmpf(T_test, thr_k, kCmpLt) & on;
           if constexpr (MODE == QR_SELECT_QUANTILE) last = in_mask(on) ? pos - lo + 1 : last;
           T = in_mask(on & ~cross) ? T_test : T;
           if (cross == 0ull) continue;
+          if constexpr (Sink::kPauses) {
+            if (__builtin_expect((cross & full) != 0ull, 0)) {
+              const uint64_t c = cross & full, c2 = c | (c >> 1);
+              const uint64_t pause = ((c2 | (c2 >> 2)) & 0x1111111111111111ull) * 15ull & live;  // whole groups
+              cross &= ~pause;
+              live &= ~pause;
+              st.from = in_mask(pause) ? pos : st.from;
+              if (cross == 0ull) continue;
+            }
+          }
           const float w = TQ * alpha;
           if (in_mask(cross)) {
             TQ = TQ * (1.f - alpha);
@@ -421,6 +454,10 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
             if (MODE != QR_SELECT_QUANTILE || !end) T = T_test;
           }
           sink.add(cross, w, pos, j + u);
+          if constexpr (Sink::kPauses) {
+            full = wave_ballot(sink.cnt == sink.cap);
+            thr_k = in_mask(full) ? INFINITY : thr_k;  // the group's next entry crosses, and finds it full
+          }
         }
         live &= ~wave_ballot(end);
       }
@@ -449,6 +486,10 @@ __device__ __forceinline__ PixelSel quantile_walk(const GView& v, int lo, int hi
     // 1 / sum, of the sum itself
     return PixelSel{ns, TQ, T, last, staged, ns > 0 ? 1.f / sum : 0.f};
   }
+  st.T = T;
+  st.TQ = TQ;
+  st.k = k;
+  st.last = last;
   return PixelSel{sink.ns, TQ, T, last, staged, sink.ns > 0 ? 1.f / (1.f - TQ) : 0.f};
 }
 

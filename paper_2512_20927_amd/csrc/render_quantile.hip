@@ -87,15 +87,24 @@ __device__ __forceinline__ void store_out4(QR_GLOBAL float* out, int64_t pix, in
   }
 }
 
+// (what the same lane stored there + v) * scale, float32 maps.
+__device__ __forceinline__ void add_out4(QR_GLOBAL float* out, int64_t pix, int dim, int c4, float4 v, float scale) {
+  const f32x4 x = *(reinterpret_cast<const QR_GLOBAL f32x4*>(out + pix * dim) + c4);
+  store_out4<QR_F32>(out, pix, dim, c4,
+                     make_float4((x.x + v.x) * scale, (x.y + v.y) * scale, (x.z + v.z) * scale, (x.w + v.w) * scale));
+}
+
 // Gather-blend of one 4-pixel group (pixels p0 .. p0 + 3 of the tile) with nu
 // distinct selections: out[p] = sum_e (w_pe / (1 - T^Q_p)) f_e (the
 // normalisation is folded into the weights). Each lane owns two float4 columns per pass (512
 // features per pass for the wave); rows are taken four at a time, the last
-// two or one on their own, so no multiply is spent on padding.
-template <int DT, int OT>
+// two or one on their own, so no multiply is spent on padding. kPart: the sum
+// is added to what the map holds of the group's earlier entries, and the result
+// takes the factor scale(q).
+template <int DT, int OT, bool kPart = false, class Scale = int>
 __device__ __forceinline__ void gather_group(const GView& v, const int* ug, const float4* uw,
                                              const uint8_t* um, int p0, int nu, int tx, int ty,
-                                             int lane, int dim) {
+                                             int lane, int dim, const Scale& scale = 0) {
   const int dim4 = dim >> 2;
   for (int cb = 0; cb < dim4; cb += 128) {
     const int c0 = cb + lane, c1 = cb + 64 + lane;
@@ -119,8 +128,13 @@ __device__ __forceinline__ void gather_group(const GView& v, const int* ug, cons
       const int gx = tx * kTile + (p % kTile), gy = ty * kTile + (p / kTile);
       if (gx >= v.W || gy >= v.H) continue;
       const int64_t pix = static_cast<int64_t>(gy) * v.W + gx;
-      if (c0 < dim4) store_out4<OT>(v.out, pix, dim, c0, a0[q]);
-      if (c1 < dim4) store_out4<OT>(v.out, pix, dim, c1, a1[q]);
+      if constexpr (kPart) {
+        if (c0 < dim4) add_out4(v.out, pix, dim, c0, a0[q], scale(q));
+        if (c1 < dim4) add_out4(v.out, pix, dim, c1, a1[q], scale(q));
+      } else {
+        if (c0 < dim4) store_out4<OT>(v.out, pix, dim, c0, a0[q]);
+        if (c1 < dim4) store_out4<OT>(v.out, pix, dim, c1, a1[q]);
+      }
     }
   }
 }
@@ -131,18 +145,19 @@ __device__ __forceinline__ void gather_group(const GView& v, const int* ug, cons
 // kNarrowRows (16) row loads of a lane are requested before the first is used
 // (slots past a group's distinct count load a row of the group again and are
 // not accumulated). One memory round trip per round and 16 rows instead of
-// several per group. ug, uw, um: the wave's groups, `cap` entries each;
-// count(g): distinct selections of the wave's group g, negative: skip it.
+// several per group. ug, uw, um: the wave's entries, those of its group g from
+// first(g) on; count(g): how many, negative: skip the group. kPart, scale(p):
+// as in gather_group, for pixel p of the wave.
 // A pixel takes every row of its group, with weight 0 where it did not select
 // it; a lane whose result is not finite forms it again from the selected rows
 // alone, so that such a row reaches no pixel that did not select it.
 constexpr int kNarrowRows = 16;
 
-template <int DT, int OT, class Count>
+template <int DT, int OT, bool kPart = false, class First, class Count, class Scale = int>
 __device__ __forceinline__ void gather_groups_narrow(const GView& v, const int* ug, const float4* uw,
-                                                     const uint8_t* um, int cap,
+                                                     const uint8_t* um, const First& first,
                                                      const Count& count, int wave, int tx, int ty,
-                                                     int lane, int dim) {
+                                                     int lane, int dim, const Scale& scale = 0) {
   const int dim4 = dim >> 2;
   const int lpg_log = dim4 <= 4 ? 2 : dim4 <= 8 ? 3 : dim4 <= 16 ? 4 : 5;
   const int gpr = 64 >> lpg_log;  // groups per round
@@ -150,20 +165,21 @@ __device__ __forceinline__ void gather_groups_narrow(const GView& v, const int* 
   const int cl = min(c, dim4 - 1);  // in-bounds column to load
   for (int r0 = 0; r0 < kWaveGroups; r0 += gpr) {
     const int grp = r0 + (lane >> lpg_log);
-    const int nu = count(grp);
+    const int nu = count(grp), at = first(grp);
     float4 a[kPG];
 #pragma unroll
     for (int q = 0; q < kPG; ++q) a[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int e0 = 0; __any(e0 < nu); e0 += kNarrowRows) {
+    constexpr int kRows = kPart ? kNarrowRows / 2 : kNarrowRows;  // (registers of the paused walk)
+    for (int e0 = 0; __any(e0 < nu); e0 += kRows) {
       if (e0 < nu) {
-        float4 f[kNarrowRows];
+        float4 f[kRows];
 #pragma unroll
-        for (int e = 0; e < kNarrowRows; ++e)
-          f[e] = load_feat4_global<DT>(v.feats, v.scale, ug[grp * cap + min(e0 + e, nu - 1)], dim, 4 * cl);
+        for (int e = 0; e < kRows; ++e)
+          f[e] = load_feat4_global<DT>(v.feats, v.scale, ug[at + min(e0 + e, nu - 1)], dim, 4 * cl);
 #pragma unroll
-        for (int e = 0; e < kNarrowRows; ++e) {
+        for (int e = 0; e < kRows; ++e) {
           if (e0 + e < nu) {
-            const float4 w = uw[grp * cap + e0 + e];
+            const float4 w = uw[at + e0 + e];
             const float ws[kPG] = {w.x, w.y, w.z, w.w};
 #pragma unroll
             for (int q = 0; q < kPG; ++q) {
@@ -183,7 +199,7 @@ __device__ __forceinline__ void gather_groups_narrow(const GView& v, const int* 
 #pragma unroll
       for (int q = 0; q < kPG; ++q) a[q] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 1
-      for (int e = grp * cap; e < grp * cap + nu; ++e) {
+      for (int e = at; e < at + nu; ++e) {
         const float4 f = load_feat4_global<DT>(v.feats, v.scale, ug[e], dim, 4 * cl);
         const float4 w = uw[e];
         const float ws[kPG] = {w.x, w.y, w.z, w.w};
@@ -197,14 +213,24 @@ __device__ __forceinline__ void gather_groups_narrow(const GView& v, const int* 
         }
       }
     }
+    float s[kPG];  // from other lanes: outside the condition
+    if constexpr (kPart) {
+#pragma unroll
+      for (int q = 0; q < kPG; ++q) s[q] = scale(kPG * grp + q);
+    }
     if (nu >= 0 && c < dim4) {
       const int p0 = (wave * kWaveGroups + grp) * kPG;
 #pragma unroll
       for (int q = 0; q < kPG; ++q) {
         const int p = p0 + q;
         const int gx = tx * kTile + (p % kTile), gy = ty * kTile + (p / kTile);
-        if (gx < v.W && gy < v.H)
-          store_out4<OT>(v.out, static_cast<int64_t>(gy) * v.W + gx, dim, c, a[q]);
+        const int64_t pix = static_cast<int64_t>(gy) * v.W + gx;
+        const bool in = gx < v.W && gy < v.H;
+        if constexpr (kPart) {
+          if (in) add_out4(v.out, pix, dim, c, a[q], s[q]);
+        } else {
+          if (in) store_out4<OT>(v.out, pix, dim, c, a[q]);
+        }
       }
     }
   }
@@ -350,9 +376,10 @@ __device__ __forceinline__ void topk_tile(const GView& v, int tile, int K, int d
   int* const s_sel_pos = reinterpret_cast<int*>(dyn_lds);                 // [256][KP], tile-list positions
   float* const s_sel_w = reinterpret_cast<float*>(dyn_lds) + kTilePix * KP;  // [256][KP]
   ListSink sink{s_sel_pos + tid * KP, s_sel_w + tid * KP};
-  const PixelSel sel = quantile_walk<QR_SELECT_TOPK>(v, static_cast<int>(v.tile_offsets[tile]),
-                                                     static_cast<int>(v.tile_offsets[tile + 1]), K, t.px + 0.5f,
-                                                     t.py + 0.5f, t.inside, prm, L, sink);
+  WalkState walk;
+  const int lo = static_cast<int>(v.tile_offsets[tile]), hi = static_cast<int>(v.tile_offsets[tile + 1]);
+  const PixelSel sel = quantile_walk<QR_SELECT_TOPK, false>(v, lo, lo, hi, K, t.px + 0.5f, t.py + 0.5f, t.inside,
+                                                            prm, L, sink, walk);
   L.ns[tid] = t.inside ? sel.ns : -1;
   L.inv[tid] = sel.inv;
   wave_lds_sync();
@@ -361,7 +388,8 @@ __device__ __forceinline__ void topk_tile(const GView& v, int tile, int K, int d
   const int wave = tid >> 6;
   const int g0 = wave * kWaveGroups;
   if (dim <= 128) {
-    gather_groups_narrow<DT, OT>(v, &L.ugid[g0 * UCAP], &L.uw[g0 * UCAP], &L.umask[g0 * UCAP], UCAP,
+    gather_groups_narrow<DT, OT>(v, &L.ugid[g0 * UCAP], &L.uw[g0 * UCAP], &L.umask[g0 * UCAP],
+                                 [](int g) { return g * UCAP; },
                                  [&](int g) { return L.unum[g0 + g]; }, wave, tx, ty, lane, dim);
     gather_groups_narrow_overflow<DT, OT>(v, L, s_sel_pos, s_sel_w, KP, K, wave, tx, ty, lane, dim);
   } else {
@@ -397,7 +425,16 @@ __device__ __forceinline__ void topk_tile(const GView& v, int tile, int K, int d
 // batches; everything after the walk is wave-local. Shared LDS (the record
 // batch) is only rewritten after a barrier that every wave reaches once it has
 // finished the previous tile.
-template <int DT, int OT, int MODE>
+// kParts: groups past the capacity are taken in parts, which the map holds
+// until the last: the sums of a group's entries so far, then 1 / (1 - T^Q) with
+// the rest (float32 maps; with K <= 8 no group can get there). Each part's walk
+// goes on where the one before paused, so all parts together walk the list
+// about once. Otherwise (bfloat16 maps, which cannot hold the sums) they are
+// collected again from the start, as many as fit the wave's space in a further
+// walk. (3M pixel-sized, faint Gaussians in a 640x480 view, K = 16, most groups
+// past the capacity: 16 columns 4,830 us in further walks for two groups of a
+// wave each, 1,200 in parts, bfloat16 2,190; 512 columns 4,980, 2,100 and 2,730.)
+template <int DT, int OT, int MODE, bool kParts>
 __device__ __forceinline__ void quantile_tile(const GView& v, int tile, int K, int dim,
                                               const qr_params& prm, QuantileLds& L,
                                               int32_t* __restrict__ sel_gid_out,
@@ -413,59 +450,114 @@ __device__ __forceinline__ void quantile_tile(const GView& v, int tile, int K, i
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // the wave's entries, and the lane's group among its sixteen
-  constexpr int kWaveCap = kWaveGroups * kGroupCap;
   float4* const uw = L.uw + wave * kWaveCap;
   int* const ug = L.ugid + wave * kWaveCap;
   uint8_t* const um = L.umask + wave * kWaveCap;
   const int lg = lane >> 2, q = lane & 3;
-  const auto collect = [&](bool on, int first, int cap, bool outputs, int& cnt) {
-    GroupSink sink{reinterpret_cast<float*>(uw + first) + q, ug + first, um + first, L.gid, cap};
-    if (outputs) {
-      const int64_t at = static_cast<int64_t>(t.py * v.W + t.px) * K;
-      sink.pos_out = sel_gid_out + at;
-      sink.w_out = sel_w_out + at;
-    }
-    const PixelSel sel = quantile_walk<MODE>(v, lo, hi, K, pxc, pyc, on, prm, L, sink);
-    cnt = sink.cnt;
-    // the weights over 1 - T^Q, each lane its pixel's
-    for (int e = 0; e < min(cnt, cap); ++e) sink.uw[kPG * e] *= sel.inv;
-    wave_lds_sync();
-    return sel;
+  const int64_t sel_at = t.inside && sel_gid_out ? static_cast<int64_t>(t.py * v.W + t.px) * K : -1;
+  const auto sink_at = [&](int first, int cap) {
+    return GroupSink<kParts>{reinterpret_cast<float*>(uw + first) + q, ug + first, um + first, L.gid, cap};
   };
-  int cnt;
-  const PixelSel sel = collect(t.inside, lg * kGroupCap, kGroupCap, t.inside && sel_gid_out, cnt);
+  const auto selections_to = [&](GroupSink<kParts>& sink) {
+    if (sel_at >= 0) {
+      sink.pos_out = sel_gid_out + sel_at;
+      sink.w_out = sel_w_out + sel_at;
+    }
+  };
+  // the weights over 1 - T^Q, each lane its pixel's
+  const auto scale_weights = [&](GroupSink<kParts>& sink, int n, float inv) {
+    for (int e = 0; e < n; ++e) sink.uw[kPG * e] *= inv;
+    wave_lds_sync();
+  };
+  const auto own_first = [](int g) { return g * kGroupCap; };
+  WalkState walk;
+  auto sink = sink_at(own_first(lg), kGroupCap);
+  selections_to(sink);
+  quantile_walk<MODE, false>(v, lo, lo, hi, K, pxc, pyc, t.inside, prm, L, sink, walk);
+  // the lane's group goes on (of a group's pixels, some may have ended)
+  const auto group_paused = [&]() {
+    return ((wave_ballot(walk.from != kWalkDone) >> (lane & 60)) & 15ull) != 0ull;
+  };
+  const auto pixel_inv = [&]() { return sink.ns > 0 ? 1.f / (1.f - walk.TQ) : 0.f; };
+  bool paused = group_paused();
+  scale_weights(sink, min(sink.cnt, kGroupCap), paused ? 1.f : pixel_inv());
   if (dim <= 128) {
-    gather_groups_narrow<DT, OT>(v, ug, uw, um, kGroupCap,
+    gather_groups_narrow<DT, OT>(v, ug, uw, um, own_first,
                                  [&](int g) {
-                                   const int n = __shfl(cnt, 4 * g, 64);
+                                   const int n = __shfl(sink.cnt, 4 * g, 64);
                                    return n > kGroupCap ? -1 : n;
                                  },
                                  wave, tx, ty, lane, dim);
   } else {
     for (int g = 0; g < kWaveGroups; ++g) {
-      const int nu = __builtin_amdgcn_readlane(cnt, 4 * g);
+      const int nu = __builtin_amdgcn_readlane(sink.cnt, 4 * g);
       if (nu <= kGroupCap)
-        gather_group<DT, OT>(v, ug + g * kGroupCap, uw + g * kGroupCap, um + g * kGroupCap,
+        gather_group<DT, OT>(v, ug + own_first(g), uw + own_first(g), um + own_first(g),
                              (wave * kWaveGroups + g) * kPG, nu, tx, ty, lane, dim);
     }
   }
-  if (kPG * K > kGroupCap) {
-    // groups past the capacity, kRedoGroups of a wave per further walk
-    uint64_t redo = __ballot(cnt > kGroupCap) & 0x1111111111111111ull;
+  if constexpr (kParts) {
+    for (;;) {
+      if (tid == 0) L.go_on = kWalkDone;
+      if (!__syncthreads_or(paused)) break;
+      int from = walk.from;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) from = min(from, __shfl_xor(from, off, 64));
+      if (lane == 0) atomicMin(&L.go_on, from);
+      __syncthreads();
+      const bool open = paused;
+      sink.cnt = 0;
+      quantile_walk<MODE, true>(v, lo, __builtin_amdgcn_readfirstlane(L.go_on), hi, K, pxc, pyc, t.inside, prm, L,
+                                sink, walk);
+      paused = group_paused();
+      const float scale = paused ? 1.f : pixel_inv();
+      wave_lds_sync();
+      if (dim <= 128) {
+        const int n = open ? sink.cnt : -1;
+        gather_groups_narrow<DT, OT, true>(v, ug, uw, um, own_first, [&](int g) { return __shfl(n, 4 * g, 64); },
+                                           wave, tx, ty, lane, dim, [&](int p) { return __shfl(scale, p, 64); });
+      } else {
+        for (uint64_t todo = wave_ballot(open) & 0x1111111111111111ull; todo; todo &= todo - 1ull) {
+          const int l = __builtin_ctzll(todo), first = own_first(l >> 2);
+          gather_group<DT, OT, true>(v, ug + first, uw + first, um + first, wave * 64 + l,
+                                     __builtin_amdgcn_readlane(sink.cnt, l), tx, ty, lane, dim, [&](int p) {
+                                       return __int_as_float(
+                                           __builtin_amdgcn_readlane(__float_as_int(scale), l + p));
+                                     });
+        }
+      }
+    }
+  } else if (kPG * K > kGroupCap) {
+    // as many groups as fit the wave's space, per further walk
+    const int cnt = sink.cnt;
+    uint64_t redo = wave_ballot(cnt > kGroupCap) & 0x1111111111111111ull;
     while (__syncthreads_or(redo != 0ull)) {
-      const int g0 = redo ? __builtin_ctzll(redo) >> 2 : -1;
-      redo &= redo - 1ull;
-      const int g1 = redo ? __builtin_ctzll(redo) >> 2 : -1;
-      redo &= redo - 1ull;
-      const bool mine = lg == g0 || lg == g1;
-      int n;
-      collect(t.inside && mine, lg == g1 ? kRedoCap : 0, mine ? kRedoCap : 0, false, n);
-      for (int k = 0; k < kRedoGroups; ++k) {
-        const int g = k ? g1 : g0;
-        if (g >= 0)
-          gather_group<DT, OT>(v, ug + k * kRedoCap, uw + k * kRedoCap, um + k * kRedoCap,
-                               (wave * kWaveGroups + g) * kPG, __builtin_amdgcn_readlane(n, 4 * g), tx, ty,
+      uint64_t take = 0ull;
+      int used = 0, first = 0;
+      while (redo) {
+        const int l = __builtin_ctzll(redo), n = __builtin_amdgcn_readlane(cnt, l);
+        if (used + n > kWaveCap) break;
+        if (lg == l >> 2) first = used;
+        used += n;
+        take |= 15ull << l;
+        redo &= redo - 1ull;
+      }
+      const bool mine = in_mask(take);
+      auto again = sink_at(first, mine ? cnt : 0);
+      WalkState fresh;
+      const PixelSel s =
+          quantile_walk<MODE, false>(v, lo, lo, hi, K, pxc, pyc, t.inside && mine, prm, L, again, fresh);
+      scale_weights(again, mine ? cnt : 0, s.inv);
+      if (dim <= 128) {
+        const int n = mine ? cnt : -1;
+        gather_groups_narrow<DT, OT>(v, ug, uw, um, [&](int g) { return __shfl(first, 4 * g, 64); },
+                                     [&](int g) { return __shfl(n, 4 * g, 64); }, wave, tx, ty, lane, dim);
+      } else {
+        for (uint64_t todo = take & 0x1111111111111111ull; todo; todo &= todo - 1ull) {
+          const int l = __builtin_ctzll(todo), f = __builtin_amdgcn_readlane(first, l);
+          gather_group<DT, OT>(v, ug + f, uw + f, um + f, wave * 64 + l, __builtin_amdgcn_readlane(cnt, l), tx, ty,
                                lane, dim);
+        }
       }
     }
   }
@@ -473,23 +565,25 @@ __device__ __forceinline__ void quantile_tile(const GView& v, int tile, int K, i
   // store precedes the loads of the gather.
   if (t.inside) {
     const int pix = t.py * v.W + t.px;
-    if (v.T_q) v.T_q[pix] = sel.TQ;
-    if (v.n_sel) v.n_sel[pix] = sel.ns;
-    if (T_final_out) T_final_out[pix] = sel.T;
-    if (last_pos_out) last_pos_out[pix] = sel.last;
+    if (v.T_q) v.T_q[pix] = walk.TQ;
+    if (v.n_sel) v.n_sel[pix] = sink.ns;
+    if (T_final_out) T_final_out[pix] = walk.T;
+    if (last_pos_out) last_pos_out[pix] = walk.last;
     if (sel_gid_out) {
       // the walk has left list positions and weights
       for (int j = 0; j < K; ++j) {
         const int64_t at = static_cast<int64_t>(pix) * K + j;
-        sel_gid_out[at] = j < sel.ns ? static_cast<int>(v.sorted_gid[sel_gid_out[at]]) : -1;
-        if (j >= sel.ns) sel_w_out[at] = 0.f;
+        sel_gid_out[at] = j < sink.ns ? static_cast<int>(v.sorted_gid[sel_gid_out[at]]) : -1;
+        if (j >= sink.ns) sel_w_out[at] = 0.f;
       }
     }
   }
 }
 
-// LDS and tile function by selection rule. (UCAP: Top-K's merge capacity, 16
-// for the other rules.)
+// LDS and tile function by selection rule. UCAP: Top-K's merge capacity; for
+// the other rules kUCapLarge for groups taken in parts. (The walk that can pause
+// takes 2% longer: 16 float32 columns, one 640x480 view of 200k Gaussians, K = 8,
+// 57 and 58 us. So K <= 8, whose groups cannot overfill, keep the one that cannot.)
 template <int MODE, int UCAP>
 using TileLds = std::conditional_t<MODE == QR_SELECT_TOPK, TopkLds<UCAP>, QuantileLds>;
 
@@ -501,7 +595,8 @@ __device__ __forceinline__ void render_tile(const GView& v, int tile, int K, int
   if constexpr (MODE == QR_SELECT_TOPK)
     topk_tile<DT, OT, UCAP>(v, tile, K, dim, prm, L, dyn_lds, sel_gid_out, sel_w_out);
   else
-    quantile_tile<DT, OT, MODE>(v, tile, K, dim, prm, L, sel_gid_out, sel_w_out, T_final_out, last_pos_out);
+    quantile_tile<DT, OT, MODE, UCAP == kUCapLarge>(v, tile, K, dim, prm, L, sel_gid_out, sel_w_out, T_final_out,
+                                                    last_pos_out);
 }
 
 template <int DT, int OT, int MODE, int UCAP>
@@ -590,19 +685,24 @@ __global__ void reset_counter_kernel(uint32_t* __restrict__ c) {
 
 using namespace qr;
 
-// Instantiates QR_LAUNCH(feature dtype, output dtype, selection rule, merge
-// capacity) for the runtime values; Top-K's larger merge capacity is built for
-// float32 maps (bfloat16 maps keep 16, which is correct at any K).
+// Instantiates QR_LAUNCH(feature dtype, output dtype, selection rule, UCAP) for
+// the runtime values; Top-K's larger merge capacity is built for float32 maps
+// (bfloat16 maps keep 16, which is correct at any K).
 #define QR_DISPATCH_DT(dt, OT, SM, UC)                        \
   switch (dt) {                                               \
     case QR_F32: QR_LAUNCH(QR_F32, OT, SM, UC); break;        \
     case QR_BF16: QR_LAUNCH(QR_BF16, OT, SM, UC); break;      \
     default: QR_LAUNCH(QR_FP8_E4M3, OT, SM, UC); break;       \
   }
-#define QR_DISPATCH_OT(dt, ot, SM)                            \
+#define QR_DISPATCH_OT(dt, ot, SM, UC)                        \
   do {                                                        \
-    if ((ot) == QR_BF16) { QR_DISPATCH_DT(dt, QR_BF16, SM, kUCap) } \
-    else { QR_DISPATCH_DT(dt, QR_F32, SM, kUCap) }            \
+    if ((ot) == QR_BF16) { QR_DISPATCH_DT(dt, QR_BF16, SM, UC) } \
+    else { QR_DISPATCH_DT(dt, QR_F32, SM, UC) }               \
+  } while (0)
+#define QR_DISPATCH_K(dt, ot, SM, K)                                                             \
+  do {                                                                                           \
+    if ((ot) != QR_BF16 && kPG * (K) > kGroupCap) { QR_DISPATCH_DT(dt, QR_F32, SM, kUCapLarge) } \
+    else { QR_DISPATCH_OT(dt, ot, SM, kUCap); }                                                  \
   } while (0)
 #define QR_DISPATCH(dt, ot, sm, K)                                                          \
   do {                                                                                      \
@@ -610,12 +710,12 @@ using namespace qr;
       if ((ot) != QR_BF16 && ucap_for(K) == kUCapLarge) {                                   \
         QR_DISPATCH_DT(dt, QR_F32, QR_SELECT_TOPK, kUCapLarge)                              \
       } else {                                                                              \
-        QR_DISPATCH_OT(dt, ot, QR_SELECT_TOPK);                                             \
+        QR_DISPATCH_OT(dt, ot, QR_SELECT_TOPK, kUCap);                                      \
       }                                                                                     \
     } else if ((sm) == QR_SELECT_STRATIFIED) {                                              \
-      QR_DISPATCH_OT(dt, ot, QR_SELECT_STRATIFIED);                                         \
+      QR_DISPATCH_K(dt, ot, QR_SELECT_STRATIFIED, K);                                       \
     } else {                                                                                \
-      QR_DISPATCH_OT(dt, ot, QR_SELECT_QUANTILE);                                           \
+      QR_DISPATCH_K(dt, ot, QR_SELECT_QUANTILE, K);                                         \
     }                                                                                       \
   } while (0)
 

@@ -587,7 +587,9 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
   f32x4 raw[Shares<NW>::kBuf][4];
   sh.prime(raw);
   ListSink sink{s_pos + tid * KP, s_w + tid * KP};
-  const PixelSel sel = quantile_walk<QR_SELECT_QUANTILE>(v, lo, hi, K, pxc, pyc, inside, prm, WL, sink);
+  WalkState walk;
+  const PixelSel sel =
+      quantile_walk<QR_SELECT_QUANTILE, false>(v, lo, lo, hi, K, pxc, pyc, inside, prm, WL, sink, walk);
   const int ns = sel.ns;
   if (walker) B.inv[tid] = sel.inv;
   int* const my_pos = s_pos + tid * KP;
