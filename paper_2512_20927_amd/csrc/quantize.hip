@@ -30,12 +30,17 @@ __device__ __forceinline__ uint32_t f32_to_e4m3(float x) {
   return sign | code;
 }
 
-// Eight elements per thread: two 16-byte loads, one 16-byte store. (1M x 512:
-// 1,012 -> 522 us against the element-wise kernel below.)
+// Eight elements per thread: two 16-byte loads, one 16-byte store; the last,
+// fewer than eight, by the threads after them. (1M x 512: 1,012 -> 522 us against
+// the element-wise kernel below.)
 __global__ void __launch_bounds__(256)
-quantize_bf16_vec_kernel(int64_t count8, const float4* __restrict__ f, uint4* __restrict__ out) {
-  const int64_t i = blockIdx.x * 256LL + threadIdx.x;
-  if (i >= count8) return;
+quantize_bf16_vec_kernel(int64_t count, const float4* __restrict__ f, uint4* __restrict__ out) {
+  const int64_t i = blockIdx.x * 256LL + threadIdx.x, count8 = count >> 3;
+  if (i >= count8) {
+    const int64_t e = 7 * count8 + i;  // 8 count8 + (i - count8)
+    if (e < count) reinterpret_cast<uint16_t*>(out)[e] = f32_to_bf16(reinterpret_cast<const float*>(f)[e]);
+    return;
+  }
   const float4 a = f[2 * i], b = f[2 * i + 1];
   const auto pair = [](float x, float y) {
     return static_cast<uint32_t>(f32_to_bf16(x)) | (static_cast<uint32_t>(f32_to_bf16(y)) << 16);
@@ -143,24 +148,17 @@ extern "C" int qr_quantize_features(void* stream, int64_t n, int32_t dim, const 
   hipStream_t s = as_stream(stream);
   // The vector kernels need their accesses aligned: the float4 rows and the
   // code words of e4m3 (widths of whole float4s, up to the 1,024 that fit in
-  // registers), eight-element pieces of the whole table for bfloat16 (the rest
-  // goes to the element-wise kernel).
+  // registers), eight-element pieces of the whole table for bfloat16.
   const auto aligned = [](const void* p, size_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; };
   if (dtype == QR_BF16) {
-    int64_t count = n * dim;
-    auto* codes = static_cast<uint16_t*>(out);
-    if (aligned(features, 16) && aligned(out, 16) && count >= 8) {
-      const int64_t count8 = count / 8;
-      hipLaunchKernelGGL(quantize_bf16_vec_kernel, dim3(static_cast<unsigned>(ceil_div(count8, 256))),
-                         dim3(256), 0, s, count8, reinterpret_cast<const float4*>(features),
+    const int64_t count = n * dim;
+    if (aligned(features, 16) && aligned(out, 16))
+      hipLaunchKernelGGL(quantize_bf16_vec_kernel, dim3(static_cast<unsigned>(ceil_div(count / 8 + count % 8, 256))),
+                         dim3(256), 0, s, count, reinterpret_cast<const float4*>(features),
                          reinterpret_cast<uint4*>(out));
-      features += 8 * count8;
-      codes += 8 * count8;
-      count -= 8 * count8;
-    }
-    if (count == 0) return check_launch("qr_quantize_features");
-    hipLaunchKernelGGL(quantize_bf16_kernel, dim3(static_cast<unsigned>(ceil_div(count, 256))),
-                       dim3(256), 0, s, count, features, codes);
+    else
+      hipLaunchKernelGGL(quantize_bf16_kernel, dim3(static_cast<unsigned>(ceil_div(count, 256))),
+                         dim3(256), 0, s, count, features, static_cast<uint16_t*>(out));
   } else if (dim % 4 == 0 && dim <= 1024 && aligned(features, 16) && aligned(out, 4)) {
     const int dim4 = dim / 4;
     int lpr_log = 0;
