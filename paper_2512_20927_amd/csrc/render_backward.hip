@@ -390,7 +390,7 @@ dense_backward_geo_kernel(int W, int H, int tiles_x, int n_units, qr_params prm,
 
   // dL/d(out) of the strip for this wave's columns, as A operands: pixel
   // (ci, strip row p), columns 128 w + 32 s + 8 kb .. + 7; and <g, out>
-  const bool wcols = kGeoCols * wave < dim;  // uniform
+  const bool wcols = kGeoCols * wave < dim, full = kGeoCols * (wave + 1) <= dim;  // uniform
   bf16x8 ghi[4][4], glo[4][4];
   {
     float tp[4];
@@ -398,36 +398,54 @@ dense_backward_geo_kernel(int W, int H, int tiles_x, int n_units, qr_params prm,
     for (int p = 0; p < 4; ++p) {
       tp[p] = 0.f;
       const int gx = tx * kTile + ci, gy = ty * kTile + strip * 4 + p;
-      // all of a pixel's loads are in flight together: none under a
-      // condition, pixels and columns past the edges read a valid address
-      // and are zeroed (the kernel, 500k Gaussians at 640x480: 496 us with
-      // each step's loads under its bounds check, 480 without)
       const bool in = gx < W && gy < H;
-      const int64_t row = (static_cast<int64_t>(min(gy, H - 1)) * W + min(gx, W - 1)) * dim;
-      f32x4 g[4][2], o[4][2];
+      if (full) {
+        // all of a pixel's loads are in flight together: none under a
+        // condition, pixels past the edges read a valid address and are
+        // zeroed (the kernel, 500k Gaussians at 640x480: 496 us with each
+        // step's loads under its bounds check, 480 without)
+        const int64_t base = (static_cast<int64_t>(min(gy, H - 1)) * W + min(gx, W - 1)) * dim + kGeoCols * wave + 8 * kb;
+        f32x4 g[4][2], o[4][2];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int c = kGeoCols * wave + 32 * s + 8 * kb;
-        const int64_t base = row + (c < dim ? c : 0);
+        for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          g[s][q] = *reinterpret_cast<const QR_GLOBAL f32x4*>(grad_out + base + 4 * q);
-          o[s][q] = *reinterpret_cast<const QR_GLOBAL f32x4*>(out + base + 4 * q);
+          for (int q = 0; q < 2; ++q) {
+            g[s][q] = *reinterpret_cast<const QR_GLOBAL f32x4*>(grad_out + base + 32 * s + 4 * q);
+            o[s][q] = *reinterpret_cast<const QR_GLOBAL f32x4*>(out + base + 32 * s + 4 * q);
+          }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          float g8[8];
+          float t = 0.f;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const float x = g[s][i >> 2][i & 3];
+            t = i == 0 ? x * o[s][0][0] : t + x * o[s][i >> 2][i & 3];
+            g8[i] = in ? x : 0.f;
+          }
+          tp[p] += in ? t : 0.f;
+          split8(g8, ghi[p][s], glo[p][s]);
         }
-      }
+      } else {
+        // a wave past the width, or at its edge: only what there is (16 columns:
+        // the other loads took the backward from 239 to 261 us)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const bool live = in && kGeoCols * wave + 32 * s + 8 * kb < dim;
-        float g8[8];
-        float t = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float x = g[s][i >> 2][i & 3];
-          t = i == 0 ? x * o[s][0][0] : t + x * o[s][i >> 2][i & 3];
-          g8[i] = live ? x : 0.f;
+        for (int s = 0; s < 4; ++s) {
+          const int c = kGeoCols * wave + 32 * s + 8 * kb;
+          float g8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          if (in && c < dim) {
+            const int64_t base = (static_cast<int64_t>(gy) * W + gx) * dim + c;
+            const f32x4 a = *reinterpret_cast<const QR_GLOBAL f32x4*>(grad_out + base);
+            const f32x4 b = *reinterpret_cast<const QR_GLOBAL f32x4*>(grad_out + base + 4);
+            const f32x4 oa = *reinterpret_cast<const QR_GLOBAL f32x4*>(out + base);
+            const f32x4 ob = *reinterpret_cast<const QR_GLOBAL f32x4*>(out + base + 4);
+            g8[0] = a.x; g8[1] = a.y; g8[2] = a.z; g8[3] = a.w;
+            g8[4] = b.x; g8[5] = b.y; g8[6] = b.z; g8[7] = b.w;
+            tp[p] += a.x * oa.x + a.y * oa.y + a.z * oa.z + a.w * oa.w + b.x * ob.x + b.y * ob.y +
+                     b.z * ob.z + b.w * ob.w;
+          }
+          split8(g8, ghi[p][s], glo[p][s]);
         }
-        tp[p] += live ? t : 0.f;
-        split8(g8, ghi[p][s], glo[p][s]);
       }
     }
     // sum over the four lanes of a pixel (kb = 0..3), then over the waves
@@ -659,29 +677,31 @@ dense_backward_feat_kernel(int W, int H, int tiles_x, int n_units, int n_slices,
   // B operands: dL/d(out) of pixels 32 k + 8 kb .. + 7, column `col`
   const int col = slice * kFeatCols + 16 * wave + ci;
   const bool wcols = slice * kFeatCols + 16 * wave < dim;  // uniform
-  bf16x8 bhi[8], blo[8];
+  bf16x8 bhi[8] = {}, blo[8] = {};
+  if (wcols) {
 #pragma unroll
-  for (int k0 = 0; k0 < 8; k0 += 4) {
-    // 32 loads in flight: none under a condition, pixels and columns past the
-    // edges read a valid address and are zeroed
-    float x[4][8];
+    for (int k0 = 0; k0 < 8; k0 += 4) {
+      // 32 loads in flight: none under a condition, pixels past the edges read
+      // a valid address and are zeroed
+      float x[4][8];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+      for (int k = 0; k < 4; ++k)
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int p = 32 * (k0 + k) + 8 * kb + t;
-        const int gx = min(tx * kTile + (p % kTile), W - 1), gy = min(ty * kTile + (p / kTile), H - 1);
-        x[k][t] = grad_out[(static_cast<int64_t>(gy) * W + gx) * dim + (wcols ? col : 0)];
+        for (int t = 0; t < 8; ++t) {
+          const int p = 32 * (k0 + k) + 8 * kb + t;
+          const int gx = min(tx * kTile + (p % kTile), W - 1), gy = min(ty * kTile + (p / kTile), H - 1);
+          x[k][t] = grad_out[(static_cast<int64_t>(gy) * W + gx) * dim + col];
+        }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const int p = 32 * (k0 + k) + 8 * kb + t;
+          const int gx = tx * kTile + (p % kTile), gy = ty * kTile + (p / kTile);
+          x[k][t] = gx < W && gy < H ? x[k][t] : 0.f;
+        }
+        split8(x[k], bhi[k0 + k], blo[k0 + k]);
       }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int p = 32 * (k0 + k) + 8 * kb + t;
-        const int gx = tx * kTile + (p % kTile), gy = ty * kTile + (p / kTile);
-        x[k][t] = wcols && gx < W && gy < H ? x[k][t] : 0.f;
-      }
-      split8(x[k], bhi[k0 + k], blo[k0 + k]);
     }
   }
 
