@@ -172,6 +172,11 @@ __device__ __forceinline__ const QR_GLOBAL float* grad_row(const GView& v, const
 // rows of pixels outside it are never used), columns in blocks of 32. Waves
 // lie along the columns (a power of two of them), the rest along the pixels;
 // past NW * MS column blocks the caller makes rounds.
+// How the columns lie on the waves of a kernel: on at most half of them, the
+// others taking other pixels (up to 256 columns); a share on each (up to 512);
+// in rounds of 512. The first two are kernels of their own, as one kernel for
+// both took 3% longer at 512 columns (K = 8, 640 x 480: 295 against 284 us).
+enum : int { kSpanPart, kSpanAll, kSpanRounds };
 template <int NW>
 struct Shares {
   static constexpr int MS = 16 / NW;  // column blocks of a wave
@@ -242,7 +247,7 @@ struct Shares {
 template <bool FAR>
 constexpr int pass_slots() { return FAR ? kSlots / 2 : kSlots; }
 
-template <int DT, int NW, bool DF, bool DOT, bool FAR>
+template <int DT, int NW, bool DF, bool DOT, bool FAR, int SPAN>
 __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, BwdLds<NW>& B,
                                              float* __restrict__ s_w, int base, int nslot, bool add,
                                              const Shares<NW>& sh, f32x4 (&raw)[Shares<NW>::kBuf][4],
@@ -254,7 +259,9 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
   constexpr int PF = DT == QR_F32 ? P : 1;    // of a feature (bf16 features and e4m3 codes are exact in one)
   const int row = lane & 15, kb = lane >> 4;
   const int n_mb = (nslot + 15) >> 4;  // blocks of 16 slots (uniform)
-  const int n_sc = sh.n_sc, cgroups = sh.cgroups, pgroups = sh.pgroups, pg = sh.pg, sub0 = sh.sub0, nsub = sh.nsub;
+  const int n_sc = sh.n_sc, sub0 = sh.sub0, nsub = sh.nsub;
+  constexpr bool kAll = SPAN == kSpanAll;
+  const int cgroups = kAll ? NW : sh.cgroups, pgroups = kAll ? 1 : sh.pgroups, pg = kAll ? 0 : sh.pg;
   const bool partial = (dim & (kSub - 1)) != 0;  // the last block is half a block
 
   // B operand of D: feature rows of the slots, this wave's columns
@@ -301,9 +308,9 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
     return __builtin_shufflevector(lds_read_tr(t), lds_read_tr(t + 4 * kTS), 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
+  const bool mine = nsub > 0;  // uniform in a wave
 #pragma unroll 1
-  for (int pb = 0; pb < kBlocks; ++pb) {
-    const bool mine = pb % pgroups == pg && nsub > 0;  // uniform
+  for (int pb = pg; pb < kBlocks; pb += pgroups) {  // (pgroups divides kBlocks: as many rounds for every wave)
     if (mine) {
       const int pb_next = pb + pgroups < kBlocks ? pb + pgroups : pb;
       // A operand of dF: w / Z of slot mb * 16 + row, pixels 8 kb .. 8 kb + 7
@@ -447,12 +454,15 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
         }
       } else {
         __syncthreads();  // every wave has left its sums (and built its weights of these pixels)
-        // the waves whose tiles hold sums of these pixels: column groups of pixel
-        // group pb % pgroups that have columns
-        const int w0 = (pb % pgroups) * cgroups, nw = min(cgroups, (n_sc + MS - 1) / MS);
+        // every pixel group adds up its own block, from the tiles of the
+        // column groups that have columns (all groups between two barriers:
+        // with a block per barrier pair, the waves of the other pixel groups
+        // idle, 128 columns took 375 instead of 283 us at K = 24, 256 columns
+        // 245 instead of 203 at K = 8, 640 x 480)
+        const int nw = min(cgroups, (n_sc + MS - 1) / MS);
         const int q = threadIdx.x & (kPB - 1);
-        take(pb * kPB + q, threadIdx.x / kPB, 2 * NW,
-             reinterpret_cast<const float*>(B.stage + w0 * BwdLds<NW>::kTileBytes) + q, nw);
+        const float* const d = reinterpret_cast<const float*>(B.stage + pg * cgroups * BwdLds<NW>::kTileBytes) + q;
+        take(pb * kPB + q, threadIdx.x / kPB - 2 * cgroups * pg, 2 * cgroups, d, nw);
         __syncthreads();  // the tiles are free again
       }
     }
@@ -560,7 +570,7 @@ constexpr size_t bwd_dynamic_lds(int K) {
 // without one), and once the feature gradients that read a weight are
 // formed, the dot d_j takes its place. The sweep recomputes each weight and
 // T^Q_j from the records with the walk's own float operations.
-template <int DT, int NW, bool WIDE>
+template <int DT, int NW, int SPAN>
 __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGrad& gg, int tile,
                                                        int K, int dim, const qr_params& prm,
                                                        BwdLds<NW>& B, float* __restrict__ dyn) {
@@ -692,16 +702,16 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
   const auto pass = [&](int base, int n, auto far) {
     constexpr bool FAR = decltype(far)::value;
     masks(base, n);
-    if constexpr (!WIDE) {
+    if constexpr (SPAN != kSpanRounds) {
       if (FAR) sh.prime(raw);
-      stream_slots<DT, NW, true, true, FAR>(v, gg, B, s_w, base, n, false, sh, raw, wave, lane, dim);
+      stream_slots<DT, NW, true, true, FAR, SPAN>(v, gg, B, s_w, base, n, false, sh, raw, wave, lane, dim);
     } else {
       const int rounds = (dim + 511) / 512;
       if (gg.grad_features) {
         for (int r = 0; r < rounds; ++r) {
           const Shares<NW> shr(v, gg, r, tx, ty, wave, lane, dim);
           shr.prime(raw);
-          stream_slots<DT, NW, true, false, FAR>(v, gg, B, s_w, base, n, false, shr, raw, wave, lane, dim);
+          stream_slots<DT, NW, true, false, FAR, SPAN>(v, gg, B, s_w, base, n, false, shr, raw, wave, lane, dim);
         }
       }
       if (geo) {
@@ -709,7 +719,7 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
         for (int r = 0; r < rounds; ++r) {
           const Shares<NW> shr(v, gg, r, tx, ty, wave, lane, dim);
           shr.prime(raw);
-          stream_slots<DT, NW, false, true, FAR>(v, gg, B, s_w, base, n, r > 0, shr, raw, wave, lane, dim);
+          stream_slots<DT, NW, false, true, FAR, SPAN>(v, gg, B, s_w, base, n, r > 0, shr, raw, wave, lane, dim);
         }
       }
     }
@@ -900,12 +910,12 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
 // Two waves per SIMD (registers of the MFMA operands and accumulators).
 constexpr int kBwdWavesPerSimd = 2;
 
-template <int DT, int NW, bool WIDE>
+template <int DT, int NW, int SPAN>
 __global__ void __launch_bounds__(64 * NW, kBwdWavesPerSimd)
 quantile_backward_kernel(ViewArgs v, GradPtrs gp, int n_tiles, qr_params prm, int K, int dim) {
   extern __shared__ __attribute__((aligned(16))) float dyn_lds[];
   __shared__ BwdLds<NW> B;
-  quantile_backward_tile<DT, NW, WIDE>(to_global(v), to_global(gp), xcd_remap(blockIdx.x, n_tiles), K, dim,
+  quantile_backward_tile<DT, NW, SPAN>(to_global(v), to_global(gp), xcd_remap(blockIdx.x, n_tiles), K, dim,
                                  prm, B, dyn_lds);
 }
 
@@ -915,7 +925,7 @@ __device__ __forceinline__ GradPtrs grad_ptrs(const qr_view_grad& g) {
 
 // Many views in one launch, one workgroup per (view, tile) item, items dealt
 // to the XCDs in contiguous runs of the schedule.
-template <int DT, int NW, bool WIDE>
+template <int DT, int NW, int SPAN>
 __global__ void __launch_bounds__(64 * NW, kBwdWavesPerSimd)
 quantile_backward_batched_grid_kernel(const qr_view* __restrict__ views,
                                       const qr_view_grad* __restrict__ grads,
@@ -925,7 +935,7 @@ quantile_backward_batched_grid_kernel(const qr_view* __restrict__ views,
   __shared__ BwdLds<NW> B;
   const uint32_t packed = __builtin_amdgcn_readfirstlane(schedule[xcd_remap(blockIdx.x, n_items)]);
   const uint32_t vi = packed >> kViewShift;
-  quantile_backward_tile<DT, NW, WIDE>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
+  quantile_backward_tile<DT, NW, SPAN>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
                                  static_cast<int>(packed & kTileMask), K, dim, prm, B, dyn_lds);
 }
 
@@ -937,7 +947,7 @@ __device__ __forceinline__ uint32_t bwd_queue_begin(int64_t n_items, int q) {
   return static_cast<uint32_t>(n_items * q / kBwdXcdQueues);
 }
 
-template <int DT, int NW, bool WIDE>
+template <int DT, int NW, int SPAN>
 __global__ void __launch_bounds__(64 * NW, kBwdWavesPerSimd)
 quantile_backward_batched_kernel(const qr_view* __restrict__ views,
                                  const qr_view_grad* __restrict__ grads,
@@ -969,7 +979,7 @@ quantile_backward_batched_kernel(const qr_view* __restrict__ views,
     if (item >= n_items) break;
     const uint32_t packed = __builtin_amdgcn_readfirstlane(schedule[item]);
     const uint32_t vi = packed >> kViewShift;
-    quantile_backward_tile<DT, NW, WIDE>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
+    quantile_backward_tile<DT, NW, SPAN>(to_global(view_args(views[vi])), to_global(grad_ptrs(grads[vi])),
                                    static_cast<int>(packed & kTileMask), K, dim, prm, B, dyn_lds);
   }
 }
@@ -991,19 +1001,21 @@ static_assert(sizeof(BwdLds<4>) + 64 + bwd_dynamic_lds(QR_MAX_K) <= kCuLds, "the
 
 using namespace qr;
 
-// QR_LAUNCH(feature type, waves, columns in rounds) for the runtime values.
-#define QR_BWD_DISPATCH_NW(dt, NW, WIDE)              \
+// QR_LAUNCH(feature type, waves, how the columns lie) for the runtime values.
+#define QR_BWD_DISPATCH_NW(dt, NW, SPAN)              \
   switch (dt) {                                       \
-    case QR_F32: QR_LAUNCH(QR_F32, NW, WIDE); break;  \
-    case QR_BF16: QR_LAUNCH(QR_BF16, NW, WIDE); break; \
-    default: QR_LAUNCH(QR_FP8_E4M3, NW, WIDE); break; \
+    case QR_F32: QR_LAUNCH(QR_F32, NW, SPAN); break;  \
+    case QR_BF16: QR_LAUNCH(QR_BF16, NW, SPAN); break; \
+    default: QR_LAUNCH(QR_FP8_E4M3, NW, SPAN); break; \
   }
-#define QR_BWD_DISPATCH(dt, eight, dim)               \
-  do {                                                \
-    if ((eight) && (dim) <= 512) { QR_BWD_DISPATCH_NW(dt, 8, false) } \
-    else if (eight) { QR_BWD_DISPATCH_NW(dt, 8, true) } \
-    else if ((dim) <= 512) { QR_BWD_DISPATCH_NW(dt, 4, false) } \
-    else { QR_BWD_DISPATCH_NW(dt, 4, true) }          \
+#define QR_BWD_DISPATCH_SPAN(dt, NW, dim)                            \
+  if ((dim) <= 256) { QR_BWD_DISPATCH_NW(dt, NW, kSpanPart) }        \
+  else if ((dim) <= 512) { QR_BWD_DISPATCH_NW(dt, NW, kSpanAll) }    \
+  else { QR_BWD_DISPATCH_NW(dt, NW, kSpanRounds) }
+#define QR_BWD_DISPATCH(dt, eight, dim)                              \
+  do {                                                               \
+    if (eight) { QR_BWD_DISPATCH_SPAN(dt, 8, dim) }                  \
+    else { QR_BWD_DISPATCH_SPAN(dt, 4, dim) }                        \
   } while (0)
 
 extern "C" int qr_render_quantile_backward(void* stream, int32_t width, int32_t height,
@@ -1032,8 +1044,8 @@ extern "C" int qr_render_quantile_backward(void* stream, int32_t width, int32_t 
   const GradPtrs gp{grad_out, grad_features, grad_means2d, grad_conic_opacity};
   const bool eight = K > kBwdPairK && K <= kBwdWideK;
   const size_t lds = bwd_dynamic_lds(K);
-#define QR_LAUNCH(DT, NW, WIDE)                                                                              \
-  hipLaunchKernelGGL((quantile_backward_kernel<DT, NW, WIDE>), dim3(n_tiles), dim3(64 * NW), lds, s, v, gp, \
+#define QR_LAUNCH(DT, NW, SPAN)                                                                              \
+  hipLaunchKernelGGL((quantile_backward_kernel<DT, NW, SPAN>), dim3(n_tiles), dim3(64 * NW), lds, s, v, gp, \
                      n_tiles, *prm, K, dim)
   QR_BWD_DISPATCH(dtype, eight, dim);
 #undef QR_LAUNCH
@@ -1071,8 +1083,8 @@ extern "C" int qr_render_quantile_batched_backward(void* stream, int32_t n_views
   const size_t lds = bwd_dynamic_lds(K);
   if (n_workgroups == 0) {
     const int ni = static_cast<int>(n_items);
-#define QR_LAUNCH(DT, NW, WIDE)                                                                          \
-  hipLaunchKernelGGL((quantile_backward_batched_grid_kernel<DT, NW, WIDE>), dim3(ni), dim3(64 * NW), lds, \
+#define QR_LAUNCH(DT, NW, SPAN)                                                                          \
+  hipLaunchKernelGGL((quantile_backward_batched_grid_kernel<DT, NW, SPAN>), dim3(ni), dim3(64 * NW), lds, \
                      s, views, grads, schedule, ni, *prm, K, dim)
     QR_BWD_DISPATCH(dtype, eight, dim);
 #undef QR_LAUNCH
@@ -1080,8 +1092,8 @@ extern "C" int qr_render_quantile_batched_backward(void* stream, int32_t n_views
   }
   auto* counter = static_cast<uint32_t*>(workspace);
   hipLaunchKernelGGL(reset_bwd_counter_kernel, dim3(1), dim3(64), 0, s, counter);
-#define QR_LAUNCH(DT, NW, WIDE)                                                                           \
-  hipLaunchKernelGGL((quantile_backward_batched_kernel<DT, NW, WIDE>), dim3(n_workgroups), dim3(64 * NW), \
+#define QR_LAUNCH(DT, NW, SPAN)                                                                           \
+  hipLaunchKernelGGL((quantile_backward_batched_kernel<DT, NW, SPAN>), dim3(n_workgroups), dim3(64 * NW), \
                      lds, s, views, grads, schedule, n_items, counter, *prm, K, dim)
   QR_BWD_DISPATCH(dtype, eight, dim);
 #undef QR_LAUNCH
