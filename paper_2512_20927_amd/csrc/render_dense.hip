@@ -299,7 +299,9 @@ __device__ void dense_strip(const GView& v, int tile, int strip, int dim, const 
 
       // feature rows of the batch for this wave's first group, requested now
       // so that the loads overlap the walk (the second group's are requested
-      // before the first group's MFMAs). No branches: ids past the list are
+      // after the first group's MFMAs, into the same registers, and waited
+      // for at once: one row latency a batch is exposed at two waves per
+      // SIMD). No branches: ids past the list are
       // valid rows (weight 0), columns past the width of a partial group are
       // clamped to its first, and a group past the width (no MFMAs, nothing
       // stored) reads column 0 (their results are never stored).

@@ -20,8 +20,8 @@
 //     A tile selects a few dozen distinct Gaussians (about 20 at K = 8, 50 at
 //     K = 40 on the room scenes, against 1,200 to 2,900 pixel selections):
 //     they get slots in list order, and each pixel a mask of the slots that it
-//     selected, 32 at a time;
-//  2. one pass over dL/d(out) per 32 slots (stream_slots) for both products on
+//     selected, pass by pass (32 slots in the first, 16 in later ones);
+//  2. one stream over dL/d(out) per pass (stream_slots) for both products on
 //     v_mfma_f32_16x16x32_bf16: feature gradients dF = W^T G, W[p][s] =
 //     w_ps / Z_p, one atomic per (slot, column), and dots D = G F^T, which are
 //     written over the weights (so a selection costs 8 bytes of LDS and K up
@@ -723,7 +723,7 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
     if (s < kMaxSlots) nslotted = j + 1;
   }
 
-  // ---- feature gradients and dots, a pass for 32 slots at a time ----
+  // ---- feature gradients and dots, pass by pass ----
   // (widths up to 512: both products at once, whether or not both are asked
   // for; wider: in rounds of 512 columns, the feature gradients of all rounds
   // before the dots, which replace the weights)
@@ -949,7 +949,10 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
   }
 }
 
-// Two waves per SIMD (registers of the MFMA operands and accumulators).
+// Two waves per SIMD (registers of the MFMA operands and accumulators: up to
+// 512 columns the workgroups of four waves, four column blocks each, need all
+// 256 and spill 28 to 36 of float32 features, the persistent ones 71 to 73, and
+// 17 to 24 of the other types; eight waves and the rounds of 512 spill none).
 constexpr int kBwdWavesPerSimd = 2;
 
 template <int DT, int NW, int SPAN>
