@@ -133,6 +133,7 @@ struct BwdLds {
   int sgid[kMaxSlots];      // Gaussian id of each slot
   float sscale[kMaxSlots];  // e4m3: its row's scale
   int wtot[4];
+  int odd;  // dL/d(out) may have a value that is not finite
 };
 
 // The walk's view of the same memory (its template names the arrays).
@@ -185,7 +186,7 @@ struct Shares {
   static constexpr int kBuf = MS > 1 ? 2 : 1;
   static constexpr int kBlocks = kTilePix / kPB;
   int n_sc, cgroups, pgroups, pg, sub0, nsub;
-  int y0, ymax, c0, cmax;
+  int x0, y0, ymax, c0, cmax;
   const QR_GLOBAL float* g0;
   int64_t gstride;
 
@@ -198,6 +199,7 @@ struct Shares {
     pgroups = NW / cgroups;
     sub0 = round * NW * MS + cg * MS;
     nsub = max(0, min(MS, n_sc - cg * MS));
+    x0 = tx * kTile;
     y0 = ty * kTile;
     ymax = v.H - 1;
     c0 = sub0 * kSub + 8 * (lane >> 4);
@@ -222,6 +224,17 @@ struct Shares {
     }
   }
 };
+
+// Whether dL/d(out) has a value of the tile in column c that is not finite.
+__device__ __forceinline__ bool odd_column(const GView& v, const GGrad& gg, int x0, int y0, int dim, int c) {
+  float z = 0.f;
+#pragma unroll 1
+  for (int y = y0; y < min(y0 + kTile, v.H); ++y) {
+    const QR_GLOBAL float* g = gg.grad_out + (static_cast<int64_t>(y) * v.W + x0) * dim + c;
+    for (int x = x0; x < min(x0 + kTile, v.W); ++x, g += dim) z = fmaf(*g, 0.f, z);
+  }
+  return z != 0.f;
+}
 
 // One pass over dL/d(out) of the tile for slots base .. base + nslot - 1:
 //   DF   feature gradients dF[s][c] = sum_p (w_ps / Z_p) g_p[c], one atomic
@@ -310,37 +323,6 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
     return __builtin_shufflevector(lds_read_tr(t), lds_read_tr(t + 4 * kTS), 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
-  // Values of a block that are not finite: a product with the weight 0 of a
-  // selection that a pixel does not have is NaN, so they leave the operand of
-  // dF and are added for the selected alone. (The dots need nothing of the
-  // kind, each being one pixel's and one slot's: theirs gets the values back.)
-  // The look at every value costs 2% at 512 columns (K = 40: 500 -> 508 us).
-  const auto nonfinite = [&](int pb, int s, const f32x4(&x)[4], bf16x8(&ap)[2][P], floatx4(&ad)[2][MB]) {
-    const int c = (sub0 + s) * kSub + 8 * kb;
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      bf16x8 out{};
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float y = x[2 * rb + (i >> 2)][i & 3];
-        if (y * 0.f == 0.f || c >= dim) continue;
-#pragma unroll
-        for (int k = 0; k < P; ++k) ap[rb][k][i] = static_cast<__bf16>(0.f);
-        out[i] = static_cast<__bf16>(y);
-        const int p = pb * kPB + 16 * rb + row;
-        int j = B.sj[p];
-        for (uint32_t m = gg.grad_features ? B.smask[p] : 0u; m; m &= m - 1u, ++j)
-          atomic_add(gg.grad_features + static_cast<int64_t>(B.sgid[base + __builtin_ctz(m)]) * dim + c + i,
-                     s_w[j] * B.inv[p] * y);
-      }
-      if constexpr (DOT) {
-#pragma unroll
-        for (int nb = 0; nb < MB; ++nb)
-          ad[rb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(out, fp[s][nb][0], ad[rb][nb], 0, 0, 0);
-      }
-    }
-  };
-
   const bool mine = nsub > 0;  // uniform in a wave
 #pragma unroll 1
   for (int pb = pg; pb < kBlocks; pb += pgroups) {  // (pgroups divides kBlocks: as many rounds for every wave)
@@ -394,15 +376,6 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
           for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
             for (int i = 0; i < P; ++i) ap[rb][i] = bf16x8{};
-        }
-        if constexpr (FAR && DF) {
-          // (0 x is 0 for finite x alone)
-          float z = 0.f;
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) z = fmaf(x[i][k], 0.f, z);
-          if (__ballot(z != 0.f) != 0ull && s < nsub) nonfinite(pb, s, x, ap, ad);
         }
         // the block two steps on, into the registers just read (always a
         // load, at the end one of this pass's blocks again: under a
@@ -511,6 +484,26 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
   }
 
   if (DF && gg.grad_features) {
+    // Columns with a value that is not finite: any slot's sums of the first pass
+    // tell that there may be one (0 x is 0 for finite x alone); the later ones
+    // leave such columns out, as odd_columns has added them. (A look at every
+    // value in the later passes cost them 2% and the persistent kernels, by
+    // their registers, 4%.)
+    uint32_t odd = 0u;
+    if constexpr (!FAR) {
+      float z = 0.f;
+#pragma unroll
+      for (int s = 0; s < MS; ++s)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) z = fmaf(af[s][cb][0][0], 0.f, z);
+      if (__ballot(z != 0.f) != 0ull && lane == 0) B.odd = 1;
+    } else if (B.odd) {
+#pragma unroll 1
+      for (int k = 0; k < 2 * nsub; ++k) {
+        const int c = sub0 * kSub + 16 * k + row;
+        if (c < dim && odd_column(v, gg, sh.x0, sh.y0, dim, c)) odd |= 1u << k;
+      }
+    }
     // lane holds dF[4 kb + i][row] of each (slot block, column block)
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
@@ -524,7 +517,8 @@ __device__ __forceinline__ void stream_slots(const GView& v, const GGrad& gg, Bw
 #pragma unroll
           for (int cb = 0; cb < 2; ++cb) {
             const int c = (sub0 + s) * kSub + 16 * cb;
-            if (s < nsub && c < dim && af[s][cb][mb][i] != 0.f) atomic_add(dst + c, af[s][cb][mb][i]);
+            if (s < nsub && c < dim && af[s][cb][mb][i] != 0.f && !(FAR && ((odd >> (2 * s + cb)) & 1u)))
+              atomic_add(dst + c, af[s][cb][mb][i]);
           }
       }
     }
@@ -573,6 +567,31 @@ __device__ __forceinline__ void slotless(const GView& v, const GGrad& gg, const 
         wave_lds_sync();  // every lane has read the weight
         if (lane == 0) s_w[p * KP + j] = t;
       }
+    }
+  }
+}
+
+// Feature gradients of the tile's selections from the second pass on (pixel p:
+// s_n[p] of them from entry s_j[p] of the lists), in the columns that have a
+// value that is not finite: a product with the weight 0 of a selection that a
+// pixel does not have would be NaN, so these columns are summed selection by
+// selection. All threads of the workgroup, a column each. *s_odd: whether there
+// is one.
+__device__ __forceinline__ void odd_columns(const GView& v, const GGrad& gg, const int* __restrict__ s_j,
+                                            const uint32_t* __restrict__ s_n, const int* __restrict__ s_pos,
+                                            const float* __restrict__ s_w, const float* __restrict__ s_inv,
+                                            const int* __restrict__ s_gid, int tx, int ty, int dim,
+                                            int* __restrict__ s_odd) {
+#pragma unroll 1
+  for (int c = threadIdx.x; c < dim; c += blockDim.x) {
+    if (!odd_column(v, gg, tx * kTile, ty * kTile, dim, c)) continue;
+    *s_odd = 1;
+#pragma unroll 1
+    for (int p = 0; p < kTilePix; ++p) {
+      if (s_n[p] == 0u) continue;  // (none outside the picture)
+      const float g = grad_row(v, gg, tx, ty, p, dim)[c];
+      for (int j = s_j[p]; j < s_j[p] + static_cast<int>(s_n[p]); ++j)
+        atomic_add(gg.grad_features + static_cast<int64_t>(s_gid[s_pos[j]]) * dim + c, s_w[j] * s_inv[p] * g);
     }
   }
 }
@@ -633,6 +652,7 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
   float* const s_w = dyn;
   int* const s_pos = reinterpret_cast<int*>(dyn + bwd_list_floats(K));
   if (walker) B.bm[tid] = 0u;  // read after the walk's barriers
+  if (tid == 0) B.odd = 0;
   BwdWalkLds<NW> WL(B);
   // the first blocks of dL/d(out) are requested before the walk
   const Shares<NW> sh(v, gg, 0, tx, ty, wave, lane, dim);
@@ -769,6 +789,15 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
   };
   const int near = min(min(kSlots, nslots), B.bpre[kNearWords]);  // uniform
   if (near > 0) pass(0, near, std::false_type{});
+  if (gg.grad_features && near < nslots && (near == 0 || B.odd)) {  // uniform
+    if (walker) {
+      B.sj[tid] = tid * KP + j_next;
+      B.smask[tid] = nslotted - j_next;
+    }
+    __syncthreads();
+    odd_columns(v, gg, B.sj, B.smask, s_pos, s_w, B.inv, B.sgid, tx, ty, dim, &B.odd);
+    __syncthreads();  // the masks may be rewritten
+  }
 #pragma unroll 1
   for (int base = near; base < nslots; base += pass_slots<true>())
     pass(base, min(pass_slots<true>(), nslots - base), std::true_type{});
@@ -951,8 +980,8 @@ __device__ __forceinline__ void quantile_backward_tile(const GView& v, const GGr
 
 // Two waves per SIMD (registers of the MFMA operands and accumulators: up to
 // 512 columns the workgroups of four waves, four column blocks each, need all
-// 256 and spill 28 to 36 of float32 features, the persistent ones 71 to 73, and
-// 17 to 24 of the other types; eight waves and the rounds of 512 spill none).
+// 256 and spill 27 to 30 of float32 features, the persistent ones 61 to 73, and
+// 14 to 21 of the other types; eight waves and the rounds of 512 spill none).
 constexpr int kBwdWavesPerSimd = 2;
 
 template <int DT, int NW, int SPAN>
