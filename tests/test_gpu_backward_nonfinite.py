@@ -71,3 +71,42 @@ def test_later_slots_take_their_own_pixels_only(qr, K, dim, storage):
     assert not np.isfinite(gf[hit][:, cols]).any()
     assert np.isfinite(gm[~hit]).all() and np.isfinite(gc[~hit]).all()
     assert not np.isfinite(gc[hit]).all()
+
+
+@pytest.mark.parametrize("near", [0, 6])
+@pytest.mark.parametrize("K,dim", [(3, 64), (24, 144), (4, 512), (50, 528)])
+def test_selections_far_down_the_list_take_their_own_pixels_only(qr, K, dim, near):
+    """The same past list position 2,048, with and without selections before it."""
+    rng = np.random.default_rng(dim + K)
+    n, fill = 25, 2048  # Gaussian 0 fills the list; pairs of small ones lie over the tile
+    spots = np.stack(np.meshgrid([2.5, 6.5, 10.5, 14.5], [3.0, 8.0, 13.0]), -1).reshape(-1, 2)
+    means = np.concatenate([[[8.0, 8.0]], np.repeat(spots, 2, 0) + rng.uniform(-0.6, 0.6, (24, 2))]).astype(np.float32)
+    co = np.tile(np.float32([0.8, 0.1, 0.9, 0.0]), (n, 1))
+    co[1:, 3] = rng.uniform(0.5, 0.9, n - 1)
+    ids = np.concatenate([1 + np.arange(near), np.zeros(fill - near, int), 1 + near + np.arange(n - 1 - near)])
+    offs, gid = _t(np.int32([0, len(ids)])), _t(ids.astype(np.int32))
+    m, c, feats = _t(means), _t(co), _t(rng.standard_normal((n, dim)).astype(np.float32))
+    prm = qr.RenderParams()
+    r = qr.render_quantile(qr.Projected(m, c, None, None, None), qr.Bins(offs, gid, None, len(ids)), feats, 16, 16, K,
+                           prm, debug=True)
+    sel = r["sel_gid"].view(256, K).cpu().numpy()
+    cols = np.arange(1, dim, 7)
+    bad = [16 * 13 + 14, 16 * 12 + 14]  # two pixels near the last spot
+    g0 = rng.standard_normal((256, dim)).astype(np.float32)
+    g0[bad] = 0.0
+    g = g0.copy()
+    g[bad[0], cols], g[bad[1], cols] = np.inf, np.nan
+
+    def run(grad):
+        gf, gm, gc = (torch.zeros(n, k, device="cuda") for k in (dim, 2, 4))
+        qr._lib.qr_render_quantile_backward(16, 16, prm.c(), K, offs, gid, m, c, feats, None,
+                                            _t(grad.reshape(16, 16, dim)), gf, gm, gc)
+        return gf.cpu().numpy()
+
+    gf, want, mag = run(g), run(g0), run(np.abs(g0))
+    hit = np.isin(np.arange(n), sel[bad][sel[bad] >= 0])
+    far = np.arange(n) > near
+    assert (far & hit).any() and (far & ~hit).sum() > 8
+    close = np.abs(gf - want) <= 2.0 ** -19 * mag + 1e-30
+    assert close[:, np.setdiff1d(np.arange(dim), cols)].all() and close[far & ~hit].all()
+    assert not np.isfinite(gf[far & hit][:, cols]).any()
